@@ -19,7 +19,7 @@ LIB = os.path.join(HERE, "librelation.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 
 ARCH = "gfx950"
-SOURCES = ["fwd.hip", "bwd.hip", "rows.hip", "layer.hip", "decode.hip", "linear.hip", "measure.hip",
+SOURCES = ["fwd.hip", "bwd.hip", "rows.hip", "layer.hip", "decode.hip", "linear.hip", "linear_bf16.hip", "measure.hip",
            "relation_api.cpp"]
 
 # Packed fp32 VALU instructions are disabled for all device code.

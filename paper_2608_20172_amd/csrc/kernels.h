@@ -177,14 +177,22 @@ struct LinearArgs {
   // normalised coordinates are formed): channel j with channel j + rope_half
   // (j < rope_half) by the angle of the token's position, from a table of
   // (cos, sin) at the chunk starts and the offsets inside a chunk
-  // (launch_linear_rope_table). Null: no rotation. The norms and p1 . p2 do not change.
+  // (launch_linear_rope_table; bf16: launch_linear_bf16_rope_table). Null: no rotation. The norms and p1 . p2 do not change.
   const float2* rope;
   int rope_half;
   int split;             // 1: D = 64 sub-problem kernels of a D = 128 backward
-  float* qn;             // [N, T, 128] fp32 (split): qt = S ^p1
+  float* qn;             // [N, T, 128] fp32 (split): qt = S ^p1. bf16, D >= 64: [N, T, D], q of blocks with a steep decay
   float* kn;             // [N, T, 128] fp32 (split): kt = S ^p2
   float* part;           // [8][N, T, 128] fp32 (split): dqt from E = 0, 1; dkt from E = 0, 1;
                          // dv from A = 0, 1 (A = 0 holds the dY of Y = I~ + E); dg from E = 0, 1
+  // bf16 kernels (linear_bf16.hip): segments of `seg` chunks. cprev and gout
+  // hold, per chunk, the state before it (the gradient of the state after it)
+  // from a zero start at the segment's edge; segc and segp the state entering
+  // (the gradient leaving) each segment; gpre and gsuf [N, nchunks, D] the
+  // retention of the segment's chunks before (after) the chunk.
+  int seg;
+  float* gpre;
+  float* gsuf;
 };
 
 // Measurement aid: if armed for kernel `name`, returns the event pair to record
@@ -209,6 +217,12 @@ int linear_chunk();
 int linear_scan_segment();  // chunks per segment of the state scans
 hipError_t launch_linear_fwd(const LinearArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_linear_bwd(const LinearArgs& a, int dtype, hipStream_t stream);
+// bf16 inputs (linear_bf16.hip): chunks per segment of its state kernel, and the passes.
+int linear_bf16_segment(int64_t heads, int nchunks);
+size_t linear_bf16_rope_bytes(int nchunks, int rope_dim);
+hipError_t launch_linear_bf16_rope_table(float2* tab, int nchunks, int rope_dim, double base, hipStream_t stream);
+hipError_t launch_linear_bf16_fwd(const LinearArgs& a, hipStream_t stream);
+hipError_t launch_linear_bf16_bwd(const LinearArgs& a, hipStream_t stream);
 int linear_gate_segment();  // tokens per segment of the gate's parameter-gradient sums
 // RoPE table of the Linear Relation kernels: (linear_chunk() + chunks) x rope_dim/2 (cos, sin)
 hipError_t launch_linear_rope_table(float2* tab, int T, int rope_dim, double base, hipStream_t stream);

@@ -1210,16 +1210,47 @@ static int linear_segments(const rel_problem* p) {
 // problems of 64 channels per head (split): its chunk states are those of
 // 4 B H heads of width 64, and it adds qt and kt of every row and eight
 // planes of partial gradients (fp32, [B H, T, 128] each).
+// With bf16 inputs (linear_bf16.hip) the states are kept per chunk from a zero
+// start at its segment and per segment; a segment of one chunk needs the latter
+// only. Longer segments get the room of two-chunk ones, the largest need, so
+// that a workspace sized for a sequence serves every shorter one.
 struct LinearPlan {
   size_t dstate, gamma, cprev, segc, segg, total;  // forward
   size_t pstate, gout, segp, total_bwd;            // backward
   size_t qn, kn, part;                             // split backward
   size_t gpart, total_gated;                       // gated backward: the gate's segment sums
+  size_t gpre, gsuf;                               // bf16: retention before and after a chunk in its segment
+  int seg, nseg;                                   // bf16: chunks per segment, segments
 };
 
-static bool linear_split(const rel_problem* p) { return p->D == 128; }
+static bool linear_split(const rel_problem* p) { return p->D == 128 && p->dtype == REL_F32; }
+
+static LinearPlan plan_linear_bf16(const rel_problem* p) {
+  LinearPlan L{};
+  const size_t N = (size_t)(p->B * p->H), nc = (size_t)linear_chunks(p), D = (size_t)p->D;
+  L.seg = rel::linear_bf16_segment((int64_t)N, (int)nc);
+  L.nseg = (int)((nc + L.seg - 1) / L.seg);
+  const size_t chunks = L.seg > 1 ? N * nc * D * D * 4 : 0;  // bytes before the segments' states
+  const size_t states = align256(N * (L.seg > 1 ? nc + (nc + 1) / 2 : nc) * D * D * 4), rows = align256(N * nc * D * 4);
+  L.cprev = 0;
+  L.segc = chunks;
+  L.gpre = states;
+  L.segg = L.gpre + rows;
+  L.total = L.segg + rows;
+  L.gout = L.total;
+  L.segp = L.gout + chunks;
+  L.gsuf = L.gout + states;
+  L.qn = L.gsuf + rows;
+  L.total_bwd = L.qn + (D >= 64 ? align256(N * (size_t)p->T * D * 4) : 0);
+  // width 128 promises its callers ten fp32 planes of the inputs' size; the layout above fits in them
+  if (D == 128) L.total_bwd = std::max(L.total_bwd, 10 * align256(N * (size_t)p->T * D * 4));
+  L.gpart = L.total_bwd;
+  L.total_gated = L.gpart + align256(N * nc * 2 * D * 4);
+  return L;
+}
 
 static LinearPlan plan_linear(const rel_problem* p, bool split) {
+  if (p->dtype == REL_BF16) return plan_linear_bf16(p);
   LinearPlan L{};
   const size_t N = (size_t)(p->B * p->H) * (split ? 4 : 1), nc = (size_t)linear_chunks(p);
   const size_t D = split ? (size_t)p->D / 2 : (size_t)p->D;
@@ -1265,10 +1296,17 @@ static void set_linear_workspace(rel::LinearArgs& a, const LinearPlan& L, char* 
   a.cprev = (float*)(ws + L.cprev);
   a.segc = (float*)(ws + L.segc);
   a.segg = (float*)(ws + L.segg);
+  a.gpre = (float*)(ws + L.gpre);
+  if (L.seg) {
+    a.seg = L.seg;
+    a.nseg = L.nseg;
+  }
   if (backward) {
     a.pstate = (float*)(ws + L.pstate);
     a.gout = (float*)(ws + L.gout);
     a.segp = (float*)(ws + L.segp);
+    a.gsuf = (float*)(ws + L.gsuf);
+    a.qn = (float*)(ws + L.qn);
   }
   if (L.part) {
     a.qn = (float*)(ws + L.qn);
@@ -1299,6 +1337,7 @@ static rel_status check_rope(const rel_problem* p, int32_t rope_dim, float rope_
 }
 
 static size_t rope_table_bytes(const rel_problem* p, int32_t rope_dim) {
+  if (rope_dim > 0 && p->dtype == REL_BF16) return align256(rel::linear_bf16_rope_bytes(linear_chunks(p), rope_dim));
   const size_t rows = (size_t)linear_chunks(p) + (size_t)rel::linear_chunk();
   return rope_dim > 0 ? align256(rows * (size_t)(rope_dim / 2) * 8) : 0;
 }
@@ -1315,7 +1354,10 @@ static rel_status set_rope(rel::LinearArgs& a, const rel_problem* p, int32_t rop
                            size_t off, hipStream_t stream) {
   if (rope_dim == 0) return REL_OK;
   float2* tab = (float2*)(ws + off);
-  const hipError_t e = rel::launch_linear_rope_table(tab, (int)p->T, (int)rope_dim, (double)rope_base, stream);
+  const hipError_t e =
+      p->dtype == REL_BF16
+          ? rel::launch_linear_bf16_rope_table(tab, linear_chunks(p), (int)rope_dim, (double)rope_base, stream)
+          : rel::launch_linear_rope_table(tab, (int)p->T, (int)rope_dim, (double)rope_base, stream);
   if (e != hipSuccess) return hip_fail(e, "RoPE table launch");
   a.rope = tab;
   a.rope_half = rope_dim / 2;

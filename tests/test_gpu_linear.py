@@ -396,3 +396,45 @@ def test_linear_gated_rope(width, padded, T, dtype):
         da_terms[0, h], dt_terms[0, h] = ref_b["dg"] * g, gb["dr"]
     _assert_param_grad("da_log", _np(o["da_log"])[:, :width], da_ref, da_terms, dtype)
     _assert_param_grad("ddt_bias", _np(o["ddt_bias"])[:, :width], dt_ref, dt_terms, dtype)
+
+
+@pytest.mark.parametrize("H,T,D,steep", [
+    (2, 15, 64, True), (2, 16, 32, False), (2, 63, 128, True), (2, 81, 64, True), (2, 16 * 64 + 1, 32, True),
+    (64, 17 * 64 - 3, 64, True), (64, 17 * 64 + 16, 128, False), (72, 57 * 64 + 1, 32, True),
+])
+def test_linear_bf16_blocks_and_segments(H, T, D, steep):
+    """The bf16 kernels at the edges of their 16-token blocks and 64-token
+    chunks, and with segments of 1 (up to 16 and more of them), 2 and 8 chunks
+    whose last one is ragged, forward and backward, the first and the last head
+    against the oracle. steep: in every second chunk some channels (single ones
+    and a run of eight) decay by up to e^-20 per token, past the range that the
+    products' reference points cover, and the others stay slow.
+
+    A rounding to bf16 changes a value by at most 2^-9 of it, and so, over sums
+    whose terms it changes independently, the result's relative l2 by as much.
+    state: the write k e^(b_end - b) is rounded once; y: that, the scores' two
+    operands and y itself; dv: its scores' two operands, the scores and dv
+    itself; dp1 and dp2: only they themselves, as their products keep fp32
+    accuracy; dg: nothing, fp32 rounding alone."""
+    x = _prep(1, H, T, D, "bf16", seed=2300 + T + D, gmax=0.05)
+    if steep:
+        rng = np.random.default_rng(2301 + T)
+        at = np.ix_([0], range(H), np.flatnonzero((np.arange(T) // 64) % 2 == 0), [3, *range(8, 16), D - 1])
+        g = x["gr"].copy()
+        g[at] = -20.0 * rng.uniform(0.0, 1.0, g[at].shape)
+        x["g"] = torch.from_numpy(g.astype(np.float32)).cuda()
+        x["gr"] = g.astype(np.float32).astype(np.float64)
+    log(f"[linear bf16 blocks] H={H} T={T} D={D} steep={steep}")
+    f = R.relation_linear_fwd(x["p1"], x["p2"], x["v"], x["g"], want_state=True)
+    o = R.relation_linear_bwd(x["p1"], x["p2"], x["v"], x["g"], x["dy"])
+    torch.cuda.synchronize()
+    rel = lambda a, b: float(np.linalg.norm(a - b) / np.linalg.norm(b))
+    roundings = {"state": 1, "y": 4, "dv": 4, "dp1": 1, "dp2": 1, "dg": 0}
+    for h in (0, H - 1):
+        args = x["p1r"][0, h], x["p2r"][0, h], x["vr"][0, h], x["gr"][0, h]
+        rf, rb = LO.forward(*args), LO.backward(*args, x["dyr"][0, h])
+        err = {"y": rel(_np(f["o"])[0, h], rf["Y"]), "state": rel(_np(f["state"])[0, h], rf["C"])}
+        err |= {n: rel(_np(o[n])[0, h], rb[n]) for n in ("dp1", "dp2", "dv", "dg")}
+        log(f"  head {h}: " + " ".join(f"{n} {e:.1e}" for n, e in err.items()))
+        for n, e in err.items():
+            assert e <= roundings[n] * 2.0 ** -9 + 1e-4, f"{n}[0,{h}]: {e}"
