@@ -23,7 +23,9 @@ namespace rel {
 
 namespace {
 
-constexpr int kDT = 256;      // threads of the states kernel
+constexpr int kDT = 256;      // threads of the states kernel, and of the merge
+constexpr int kDTFew = 1024;  // threads of the states kernel where workgroups are few
+constexpr int kFewGroups = 512;
 constexpr int kSlice = 256;   // keys per workgroup in relation_decode
 constexpr int kUnroll = 2;    // keys per lane group whose loads are in flight together
 
@@ -78,10 +80,18 @@ __device__ __forceinline__ void merge_into(float& m, float& l, float (&z)[VEC], 
 
 // Exchange state of keys [j0, j1) of one (b, h) row, split into a.nsplit slices
 // (grid: nsplit x B*H); keys at or after the row's own entry are never read.
-template <typename TI, int VEC, int LPK>
-__global__ __launch_bounds__(kDT) void decode_states_kernel(DecodeArgs a) {
+//
+// NT = kDT threads read a slice of 256 keys in several steps of the loop, which
+// needs other workgroups on the CU to fill the waits. With fewer than
+// kFewGroups workgroups (two per CU) NT = kDTFew: the same slice in one step or
+// two. Whole steps (with the merge), 256 against 1024 threads: 9.3 and 8.4 us at
+// 4 workgroups, 12.5 and 9.9 at 32 (D = 128), 17.4 and 13.0 at 256 (D = 128);
+// 12.8 and 14.0 at 512 (D = 64), 15.4 and 20.2 at 768. (Four keys per lane
+// group in flight instead of kUnroll: 139 -> 182 us at 12288 workgroups.)
+template <typename TI, int VEC, int LPK, int NT>
+__global__ __launch_bounds__(NT) void decode_states_kernel(DecodeArgs a) {
   constexpr int KPW = 64 / LPK;          // keys per wave and step
-  constexpr int NW = kDT / 64;
+  constexpr int NW = NT / 64;
   __shared__ float red[NW][2 + 128];
   const int slice = blockIdx.x;
   const int n = blockIdx.y;              // b * H + h
@@ -144,16 +154,19 @@ __global__ __launch_bounds__(kDT) void decode_states_kernel(DecodeArgs a) {
       }
     }
   }
-  // merge the lane groups of the wave (lanes with equal c hold the same channels)
+  // merge the lane groups of a wave (lanes with equal c hold the same channels)
+  auto merge_groups = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int o = LPK; o < 64; o <<= 1) {
-    float zo[VEC];
-    const float mo = __shfl_xor(m, o, 64), lo = __shfl_xor(l, o, 64);
+    for (int o = LPK; o < 64; o <<= 1) {
+      float zo[VEC];
+      const float mo = __shfl_xor(m, o, 64), lo = __shfl_xor(l, o, 64);
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) zo[e] = __shfl_xor(z[e], o, 64);
-    merge_into<VEC>(m, l, z, mo, lo, zo);
-  }
-  // then the waves, in a fixed order
+      for (int e = 0; e < VEC; ++e) zo[e] = __shfl_xor(z[e], o, 64);
+      merge_into<VEC>(m, l, z, mo, lo, zo);
+    }
+  };
+  merge_groups();
+  // then the waves, in a fixed order: group kg of the first wave takes waves kg, kg + KPW, ...
   if (kg == 0) {
     if (c == 0) {
       red[w][0] = m;
@@ -165,13 +178,19 @@ __global__ __launch_bounds__(kDT) void decode_states_kernel(DecodeArgs a) {
     }
   }
   __syncthreads();
-  if (w == 0 && kg == 0) {
-    for (int ow = 1; ow < NW; ++ow) {
-      float zo[VEC];
+  if (w != 0) return;
+  m = kNegInf;
+  l = 0.0f;
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) zo[e] = chan ? red[ow][2 + c0 + e] : 0.0f;
-      merge_into<VEC>(m, l, z, red[ow][0], red[ow][1], zo);
-    }
+  for (int e = 0; e < VEC; ++e) z[e] = 0.0f;
+  for (int ow = kg; ow < NW; ow += KPW) {
+    float zo[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) zo[e] = chan ? red[ow][2 + c0 + e] : 0.0f;
+    merge_into<VEC>(m, l, z, red[ow][0], red[ow][1], zo);
+  }
+  merge_groups();
+  if (kg == 0) {
     float* st = a.states + ((int64_t)slice * a.B * a.H + n) * (a.D + 2);
     if (c == 0) {
       st[0] = m;
@@ -185,13 +204,19 @@ __global__ __launch_bounds__(kDT) void decode_states_kernel(DecodeArgs a) {
 }
 
 // One workgroup per (b, h) row: merge the row's a.nstates states, then Self
-// and the count correction (eqs. 12-13) at i = the row's cache length. Lanes
-// run over states and wave w over channels 32 w .. 32 w + 31, so the loads of
-// all states are in flight at once; the lane sums then meet by shuffles.
-template <typename TI>
-__global__ __launch_bounds__(256) void decode_merge_kernel(DecodeArgs a) {
-  __shared__ float zsh[128];
-  __shared__ float lsh;
+// and the count correction (eqs. 12-13) at i = the row's cache length. A lane
+// holds a channel pair and G lanes a state, so that a state is read as one run
+// of memory; lane group g takes the states g, g + kDT / G, ..., kBatch of them in
+// flight, against its own running maximum, and the groups meet in LDS. Bound
+// by latency: one round of reads for up to kBatch kDT / G states (64 at D = 64).
+// With lanes over states and 32 channels each, whose sums met in 192 shuffles,
+// the step took 12.6 us for 16 rows of 16 states and 34.6 us for 16 of 128;
+// it takes 10.0 and 31.1 (256 threads in the states kernel).
+template <typename TI, int G>
+__global__ __launch_bounds__(kDT) void decode_merge_kernel(DecodeArgs a) {
+  constexpr int NG = kDT / G, kBatch = 8;
+  __shared__ float mls[NG][2];
+  __shared__ float zsh[NG][2 * G];
   const int n = blockIdx.x;  // b * H + h
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int b = n / a.H, h = n % a.H;
@@ -212,43 +237,58 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeArgs a) {
       vi1 = Elem<TI>::load((const TI*)a.v + selfrow + lane + 64);
     }
   }
-  float m = kNegInf;
-  for (int s = lane; s < a.nstates; s += 64) m = fmaxf(m, st0[s * stride_s]);
-  for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-  const int cb = 32 * w;
-  if (cb < a.D) {  // wave-uniform
-    float acc[32];
+  const int grp = tid / G, c0 = 2 * (tid % G);
+  const int cz = c0 < a.D ? c0 : 0;  // lanes past the width repeat the first pair; nobody reads theirs
+  float m = kNegInf, l = 0.0f, z[2] = {0.0f, 0.0f};
+  for (int s0 = grp; s0 < a.nstates; s0 += NG * kBatch) {
+    float2 ml[kBatch], zz[kBatch];
 #pragma unroll
-    for (int e = 0; e < 32; ++e) acc[e] = 0.0f;
-    float l = 0.0f;
-    for (int s = lane; s < a.nstates; s += 64) {
-      const float* st = st0 + s * stride_s;
-      const float ms = st[0];
-      const float f = ms == kNegInf ? 0.0f : fast_exp2((ms - m) * kLog2e);
-      l = __builtin_fmaf(st[1], f, l);
-      const float2* zp = reinterpret_cast<const float2*>(st + 2 + cb);  // 8-byte aligned: D + 2 and cb even
+    for (int k = 0; k < kBatch; ++k) {  // slots past the end read the last state and count for nothing
+      const float* st = st0 + min(s0 + k * NG, a.nstates - 1) * stride_s;
+      ml[k] = *reinterpret_cast<const float2*>(st);  // 8-byte aligned: D + 2 and c0 even
+      zz[k] = *reinterpret_cast<const float2*>(st + 2 + cz);
+    }
+    float mn = m;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float2 zz = zp[e];
-        acc[2 * e] = __builtin_fmaf(zz.x, f, acc[2 * e]);
-        acc[2 * e + 1] = __builtin_fmaf(zz.y, f, acc[2 * e + 1]);
+    for (int k = 0; k < kBatch; ++k) {
+      if (s0 + k * NG >= a.nstates) {
+        ml[k] = float2{kNegInf, 0.0f};
+        zz[k] = float2{0.0f, 0.0f};
       }
+      mn = fmaxf(mn, ml[k].x);
     }
+    const float f0 = m == kNegInf ? 0.0f : fast_exp2((m - mn) * kLog2e);
+    l *= f0;
+    z[0] *= f0;
+    z[1] *= f0;
 #pragma unroll
-    for (int e = 0; e < 32; ++e)
-      for (int o = 32; o >= 1; o >>= 1) acc[e] += __shfl_xor(acc[e], o, 64);
-    for (int o = 32; o >= 1; o >>= 1) l += __shfl_xor(l, o, 64);
-    if (lane == 0) {
-#pragma unroll
-      for (int e = 0; e < 32; ++e) zsh[cb + e] = acc[e];
-      if (w == 0) lsh = l;
+    for (int k = 0; k < kBatch; ++k) {
+      const float f = ml[k].x == kNegInf ? 0.0f : fast_exp2((ml[k].x - mn) * kLog2e);
+      l = __builtin_fmaf(ml[k].y, f, l);
+      z[0] = __builtin_fmaf(zz[k].x, f, z[0]);
+      z[1] = __builtin_fmaf(zz[k].y, f, z[1]);
     }
+    m = mn;
   }
+  if (c0 == 0) {
+    mls[grp][0] = m;
+    mls[grp][1] = l;
+  }
+  *reinterpret_cast<float2*>(&zsh[grp][c0]) = float2{z[0], z[1]};
   __syncthreads();
   if (w != 0) return;  // the first wave finishes the row
-  const float l = lsh;
-  const float z0 = lane < a.D ? zsh[lane] : 0.0f;
-  const float z1 = lane + 64 < a.D ? zsh[lane + 64] : 0.0f;
+  m = kNegInf;
+#pragma unroll
+  for (int x = 0; x < NG; ++x) m = fmaxf(m, mls[x][0]);
+  l = 0.0f;
+  float z0 = 0.0f, z1 = 0.0f;
+#pragma unroll
+  for (int x = 0; x < NG; ++x) {
+    const float mx = mls[x][0], f = mx == kNegInf ? 0.0f : fast_exp2((mx - m) * kLog2e);
+    l = __builtin_fmaf(mls[x][1], f, l);
+    z0 = __builtin_fmaf(zsh[x][lane], f, z0);
+    if (G > 32) z1 = __builtin_fmaf(zsh[x][64 + lane], f, z1);
+  }
   // Self: U_ii = scale q . k_i, S = sigmoid(U_ii / tau_S)
   for (int o = 32; o >= 1; o >>= 1) d += __shfl_xor(d, o, 64);
   const float S = 1.0f / (1.0f + expf(-d * a.scale * a.inv_tau));
@@ -274,18 +314,36 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeArgs a) {
   if (lane == 0 && a.row_stat) a.row_stat[n] = valid ? lnZ + lam * ln_i : nan;
 }
 
+template <typename TI, int VEC, int LPK>
+void launch_states_l(const DecodeArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)a.nsplit, (unsigned)(a.B * a.H));
+  if ((int64_t)a.nsplit * a.B * a.H < kFewGroups)
+    hipLaunchKernelGGL((decode_states_kernel<TI, VEC, LPK, kDTFew>), grid, dim3(kDTFew), 0, stream, a);
+  else
+    hipLaunchKernelGGL((decode_states_kernel<TI, VEC, LPK, kDT>), grid, dim3(kDT), 0, stream, a);
+}
+
 template <typename TI, int VEC>
 hipError_t launch_states_t(const DecodeArgs& a, hipStream_t stream) {
-  const dim3 grid((unsigned)a.nsplit, (unsigned)(a.B * a.H));
   const int lanes = (a.D + VEC - 1) / VEC;
   if (lanes <= 4)
-    hipLaunchKernelGGL((decode_states_kernel<TI, VEC, 4>), grid, dim3(kDT), 0, stream, a);
+    launch_states_l<TI, VEC, 4>(a, stream);
   else if (lanes <= 8)
-    hipLaunchKernelGGL((decode_states_kernel<TI, VEC, 8>), grid, dim3(kDT), 0, stream, a);
+    launch_states_l<TI, VEC, 8>(a, stream);
   else if (lanes <= 16)
-    hipLaunchKernelGGL((decode_states_kernel<TI, VEC, 16>), grid, dim3(kDT), 0, stream, a);
+    launch_states_l<TI, VEC, 16>(a, stream);
   else
-    hipLaunchKernelGGL((decode_states_kernel<TI, VEC, 32>), grid, dim3(kDT), 0, stream, a);
+    launch_states_l<TI, VEC, 32>(a, stream);
+  return hipGetLastError();
+}
+
+template <typename TI>
+hipError_t launch_merge_t(const DecodeArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)(a.B * a.H));
+  if (a.D <= 64)
+    hipLaunchKernelGGL((decode_merge_kernel<TI, 32>), grid, dim3(kDT), 0, stream, a);
+  else
+    hipLaunchKernelGGL((decode_merge_kernel<TI, 64>), grid, dim3(kDT), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -298,12 +356,7 @@ hipError_t launch_decode_states(const DecodeArgs& a, int dtype, hipStream_t stre
 }
 
 hipError_t launch_decode_merge(const DecodeArgs& a, int dtype, hipStream_t stream) {
-  const dim3 grid((unsigned)(a.B * a.H));
-  if (dtype == 1)
-    hipLaunchKernelGGL(decode_merge_kernel<bf16>, grid, dim3(256), 0, stream, a);
-  else
-    hipLaunchKernelGGL(decode_merge_kernel<float>, grid, dim3(256), 0, stream, a);
-  return hipGetLastError();
+  return dtype == 1 ? launch_merge_t<bf16>(a, stream) : launch_merge_t<float>(a, stream);
 }
 
 }  // namespace rel

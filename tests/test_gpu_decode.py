@@ -152,3 +152,20 @@ def test_decode_repeatable():
     b = R.relation_decode(x["q"], x["k"], x["v"], x["len"], x["lam"])
     torch.cuda.synchronize()
     assert torch.equal(a["o"], b["o"]) and torch.equal(a["row_stat"], b["row_stat"])
+
+
+@pytest.mark.parametrize("B,H,T,D,dtype", [
+    (1, 1, 2, 64, "bf16"), (1, 2, 257, 32, "bf16"), (1, 4, 2049, 128, "bf16"), (2, 8, 16385, 64, "bf16"),
+    (2, 4, 16500, 96, "bf16"), (64, 8, 300, 64, "bf16"), (1, 1, 16641, 64, "f32"), (3, 2, 2600, 128, "f32"),
+])
+def test_decode_few_and_many_states(B, H, T, D, dtype):
+    """Slices read by the wide workgroups (fewer than 512 of them) and the
+    narrow ones, and merges of 1, 2, 8, 9, 64, 65 and 66 states: less than one
+    batch of a lane group, exactly one, and a ragged second one."""
+    lens = [max(1, T - 7 * b) for b in range(B)]
+    x = _prep(B, H, T, D, dtype, seed=860 + T + D, lengths=lens, std=1.0 if dtype == "f32" else None)
+    r = R.relation_decode(x["q"], x["k"], x["v"], x["len"], x["lam"])
+    torch.cuda.synchronize()
+    Y, M = _oracle_rows(x)
+    assert_close("y", _np(r["o"]), Y, dtype)
+    assert_close("M", _np(r["row_stat"]), M, dtype)
