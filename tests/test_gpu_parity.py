@@ -448,3 +448,28 @@ def test_workload_long_context_full_head():
     err = np.abs(dv - do).max() / np.abs(do).max()
     log(f"  sum dV vs sum dO: rel err {err:.3e}")
     assert err < 2e-2
+
+
+@pytest.mark.parametrize("lam_shape,lam_dtype,expand", [((), torch.float32, False), ((1,), torch.float64, True),
+                                                         ((1, 1), torch.float32, True)])
+def test_autograd_lambda_forms_and_broadcast_gradient(lam_shape, lam_dtype, expand):
+    """lambda of any one-element shape and dtype gets a gradient of its own shape
+    and dtype, and a broadcast upstream gradient (strides 0) counts as its dense
+    copy: the same bits as relation_fwd and relation_bwd on plain tensors."""
+    g = torch.Generator().manual_seed(5)
+    q, k, v = (torch.randn(2, 100, 3, 64, generator=g).cuda().bfloat16().transpose(1, 2) for _ in range(3))
+    dout = torch.randn(2, 3, 1, 64, generator=g).cuda().bfloat16().expand(2, 3, 100, 64)
+    dout = dout if expand else dout.contiguous()
+    lam = torch.full(lam_shape, 0.5, dtype=lam_dtype, device="cuda")
+    leaves = [x.detach().requires_grad_(True) for x in (q, k, v, lam)]
+    o = R.relation(*leaves)
+    grads = torch.autograd.grad(o, leaves, dout)
+    one = torch.full((1,), 0.5, device="cuda")
+    f = R.relation_fwd(q, k, v, one)
+    b = R.relation_bwd(q, k, v, f["o"], dout.contiguous(), one, f["row_stat"])
+    torch.cuda.synchronize()
+    assert torch.equal(o, f["o"])
+    for got, n in zip(grads, ("dq", "dk", "dv")):
+        assert torch.allclose(got.float(), b[n].float(), rtol=2 ** -7, atol=2 ** -7), n  # dq's order of sums may differ
+    assert grads[3].shape == lam.shape and grads[3].dtype == lam.dtype
+    assert abs(float(grads[3]) - float(b["dlambda"])) <= 1e-4 * (1 + abs(float(b["dlambda"])))
