@@ -263,8 +263,11 @@ LayerPlan plan_layer(const rel_problem* p, const rel_layer_opts* o) {
   return L;
 }
 
-// The widest chunk (channels per thread) the caller's tensors allow: D, D/2
-// (with RoPE) and the strides must be multiples of it, the pointers aligned to it.
+// The widest chunk (channels) the caller's tensors allow: 16 bytes where D, D/2
+// (with RoPE) and the strides are multiples of it and the pointers aligned to
+// it. Narrower: in bf16 8 bytes on 4-byte boundaries (rows of 60 channels: the
+// halves of 30 start on 4-byte boundaries only), in fp32 two channels, where
+// the same are multiples of two channels, and single channels otherwise.
 int layer_vec(const rel_problem* p, const rel_layer_opts* o, std::initializer_list<const void*> ptrs) {
   const size_t es = elem_size(p->dtype);
   const int vmax = (int)(16 / es);
@@ -272,6 +275,10 @@ int layer_vec(const rel_problem* p, const rel_layer_opts* o, std::initializer_li
     bool ok = p->D % v == 0 && p->stride_t % v == 0 && p->stride_h % v == 0 && p->stride_b % v == 0;
     if (o->rope_base > 0.0) ok = ok && (p->D / 2) % v == 0;
     for (const void* x : ptrs) ok = ok && (uintptr_t)x % (v * es) == 0;
+    if (ok && v == 2 && p->dtype == REL_BF16) {
+      if (p->D < 8) continue;  // a half holds a chunk of 4
+      return 4;
+    }
     if (ok) return v;
   }
   return 1;

@@ -230,3 +230,25 @@ def test_layer_paper_geometries(name):
         log(f"  pair ({a},{b}) |sum dV| vs |sum dO|: rel err {err:.3e}")
         assert err < 2e-2
     assert np.all(np.isfinite(_np(f["o"]))) and np.all(np.isfinite(_np(g["dq"])))
+
+
+@pytest.mark.parametrize("B,H,T,D,dtype,pairing,rope", [
+    (2, 2, 70, 8, "bf16", "A", 1.0e4),     # one 8-byte chunk per half
+    (2, 2, 70, 4, "bf16", "A", 1.0e4),     # too narrow for one: single channels
+    (2, 4, 70, 36, "bf16", "B", 1.0e4),    # halves of 18: the last chunk repeats two channels
+    (2, 4, 70, 50, "bf16", "B", 1.0e4),    # odd halves: single channels
+    (2, 4, 70, 62, "bf16", "A", 0.0),      # no RoPE: 32 + 30 channels in 8-byte chunks
+    (2, 4, 70, 40, "bf16", "A", 0.0),      # 24 + 16 in 16-byte chunks
+    (2, 4, 70, 33, "bf16", "A", 0.0),      # odd width
+    (2, 2, 70, 124, "bf16", "A", 1.0e4),
+    (2, 4, 70, 36, "f32", "B", 1.0e4), (2, 4, 70, 40, "f32", "A", 1.0e4), (2, 4, 70, 10, "f32", "A", 0.0),
+    (1600, 2, 41, 32, "bf16", "A", 1.0e4),  # 65600 rows a pair: dtheta's sum in two stages
+])
+def test_layer_chunk_edges(B, H, T, D, dtype, pairing, rope):
+    """Chunks of 16 and 8 bytes and single channels at the widths where the two
+    runs of a row end inside a chunk, tensors as views of [B, T, H, D] (rows off
+    16-byte boundaries), and both forms of the sum over rows."""
+    x = _prep(B, H, T, D, dtype, seed=900 + D, std=1.0 if dtype == "f32" else None)
+    for n in ("q", "k", "v", "dout"):
+        x[n] = x[n].transpose(1, 2).contiguous().transpose(1, 2)
+    check_layer(x, dtype, pairing, rope)
