@@ -366,26 +366,41 @@ __device__ __forceinline__ bool wave_any(bool p) { return __any((int)p); }
 // is shared in that XCD's L2; within an XCD the tiles are issued in
 // decreasing order of causal work, so the longest rows start first.
 // The grid is 8 * ceil(N/8) * ntiles; ids that map past the last head exit.
+// Where that leaves XCDs short of a head (N = 4: half of them idle; 12: half
+// of them with one head of two) the heads alternate over the ids instead, the
+// grid is N * ntiles, and a head's tiles are on several XCDs: for N = 12, T =
+// 8192, D = 96 forward 256 -> 220 us, backward 885 -> 726; N = 4, T = 8192, D =
+// 64 144 -> 134 and 408 -> 396; N = 36, T = 2048 50 -> 46 (forward). With one
+// place of 15 empty or fewer the shared L2 is worth more: N = 60, T = 2048, D =
+// 128 forward 92 against 94 us, N = 100, T = 1024 35 against 44.
 // ---------------------------------------------------------------------------
 struct TileMap {
-  int N, ntiles, hpx;  // heads, tiles per head, heads per XCD
+  int N, ntiles, hpx;  // heads, tiles per head, heads per XCD (0: heads alternate)
 };
+constexpr int kSpreadWaste = 12;  // heads alternate when more than N / 12 of the XCDs' places for heads stay empty
 __host__ __device__ inline TileMap make_tilemap(int N, int ntiles) {
   TileMap m;
   m.N = N;
   m.ntiles = ntiles;
   m.hpx = (N + 7) / 8;
+  if ((8 * m.hpx - N) * kSpreadWaste > N) m.hpx = 0;
   return m;
 }
-__host__ __device__ inline long grid_size(const TileMap& m) { return 8L * m.hpx * m.ntiles; }
+__host__ __device__ inline long grid_size(const TileMap& m) { return (m.hpx ? 8L * m.hpx : (long)m.N) * m.ntiles; }
 // Returns false for an idle workgroup.
 __device__ __forceinline__ bool map_tile(const TileMap& m, int bid, int& head, int& tile,
                                          bool heavy_high) {
-  const int xcd = bid & 7;
-  const int k = bid >> 3;
-  const int slot = k % m.hpx;
-  const int round = k / m.hpx;
-  head = xcd + 8 * slot;
+  int round;
+  if (m.hpx == 0) {
+    round = bid / m.N;
+    head = bid % m.N;
+  } else {
+    const int xcd = bid & 7;
+    const int k = bid >> 3;
+    const int slot = k % m.hpx;
+    round = k / m.hpx;
+    head = xcd + 8 * slot;
+  }
   tile = heavy_high ? (m.ntiles - 1 - round) : round;
   return head < m.N && round < m.ntiles;
 }
