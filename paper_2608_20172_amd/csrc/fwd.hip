@@ -257,6 +257,17 @@ __device__ __forceinline__ RowEpilogue row_epilogue(float m_log2, float l, float
   return e;
 }
 
+__device__ __forceinline__ void store_row_stats(const FwdArgs& a, int head, int qi, const RowEpilogue& e, float lam,
+                                                float ln_i, const Lane& L) {
+  if (L.g == 0) {
+    const int64_t ridx = (int64_t)head * a.T + qi;
+    if (a.row_stat) a.row_stat[ridx] = e.lnZ + lam * ln_i;
+    if (a.self_mass) a.self_mass[ridx] = e.omg;
+    if (a.exch_mass) a.exch_mass[ridx] = e.g;
+    if (a.exch_lse) a.exch_lse[ridx] = e.LE;
+  }
+}
+
 // Row epilogue and stores for this lane's row qi from the terminal state of
 // both lanes of the row (l, uii not yet combined across the two halves).
 template <class P, int D, int QM>
@@ -286,13 +297,7 @@ __device__ __forceinline__ void finish_row(const FwdArgs& a, typename P::T* o, c
       P::store4(o + qi * st + d0, out);
     }
   }
-  if (L.g == 0) {
-    const int64_t ridx = (int64_t)head * T + qi;
-    if (a.row_stat) a.row_stat[ridx] = e.lnZ + lam * ln_i;
-    if (a.self_mass) a.self_mass[ridx] = e.omg;
-    if (a.exch_mass) a.exch_mass[ridx] = e.g;
-    if (a.exch_lse) a.exch_lse[ridx] = e.LE;
-  }
+  store_row_stats(a, head, qi, e, lam, ln_i, L);
 }
 
 // The query operand of this lane's row (times c in mode 1).
@@ -319,6 +324,11 @@ constexpr int kNT = 256;  // threads per workgroup
 template <class P, int D>
 constexpr int fwd_occupancy() {
   return sizeof(typename P::T) == 2 ? (D <= 64 ? 3 : 2) : (D <= 64 ? 2 : 1);  // waves per SIMD
+}
+
+template <class P, int D>
+constexpr int fwd_split_occupancy() {
+  return 2 * 4 * kBK * P::ROWB <= 65536 ? 2 : 1;  // by LDS
 }
 
 template <class P, int D>
@@ -432,16 +442,159 @@ __global__ __launch_bounds__(kNT, (fwd_occupancy<P, D>())) void fwd_kernel(FwdAr
   finish_row<P, D, QM>(a, o, v, st, head, qi, m, l, uii, oacc, L, c);
 }
 
+// The same pass with a block of 32 query rows per workgroup, whose four waves
+// share out the keys: wave w takes the 64-key tiles w, w + 4, ... With the
+// reference fixed at 0 the waves' l and z are plain sums, which meet in LDS;
+// each wave then finishes a quarter of the channels. Where the 128-row
+// workgroups are few, the longest one's chain of tiles is the whole time, and
+// this cuts it to a quarter (and gives four times the workgroups), at the price
+// of reading K and V once per 32 rows and of single tile buffers.
+// Measured (us, 128-row workgroups against this): N = 32, T = 512, D = 64 14.2
+// and 9.0; 4 x 4096 x 64 68.2 and 34.9; 8 x 2048 x 128 48.2 and 35.9; fp32
+// 2 x 128 x 32 14.3 and 8.9, 16 x 1024 x 64 158 and 64.
 template <class P, int D>
-void launch_one(const FwdArgs& a, hipStream_t stream) {
+__global__ __launch_bounds__(kNT, (fwd_split_occupancy<P, D>())) void fwd_split_kernel(FwdArgs a) {
+  using E = typename P::T;
+  using Op = typename P::Op;
+  constexpr int QM = qmode<P, D>();
+  constexpr int KS = D / 16, DB = D / 32, NW = kNT / 64;
+  constexpr int TB = kBK * P::ROWB;
+  constexpr int NSEG = TB / 1024;
+  constexpr int ZB = 64 * 16 * DB * 4;  // a wave's accumulators
+  static_assert(ZB <= 2 * TB, "the accumulators meet in the tiles' memory");
+  __shared__ __attribute__((aligned(1024))) unsigned char tiles[NW * 2 * TB];
+  __shared__ float lsh[NW][64], ush[NW][64];
+
+  int head, qt;
+  if (!map_tile(a.map, blockIdx.x, head, qt, true)) return;
+  const int T = a.T;
+  const int64_t st = a.st;
+  const int64_t hoff = (int64_t)(head / a.H) * a.sb + (int64_t)(head % a.H) * a.sh;
+  const E* q = (const E*)a.q + hoff;
+  const E* k = (const E*)a.k + hoff;
+  const E* v = (const E*)a.v + hoff;
+  E* o = (E*)a.o + hoff;
+
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
+  const int lane = tid & 63;
+  const Lane L(lane);
+  const int qr0 = qt * 32, qi = qr0 + L.n;  // qr0 < T
+  const float c = a.scale * kLog2e;
+  const int row_bytes = (int)(st * (int64_t)sizeof(E));
+  const __amdgpu_buffer_rsrc_t krs = make_rsrc(k, T * row_bytes);
+  const __amdgpu_buffer_rsrc_t vrs = make_rsrc(v, T * row_bytes);
+  unsigned char* Ks = tiles + w * 2 * TB;
+  unsigned char* Vs = Ks + TB;
+  auto load_tile = [&](int j0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < NSEG; ++s) dma_segment<P>(krs, Ks, s, row_bytes, j0, lane);
+#pragma unroll
+    for (int s = 0; s < NSEG; ++s) dma_segment<P>(vrs, Vs, s, row_bytes, j0, lane);
+  };
+  const int nkt = (min(qr0 + 32, T) - 1) / kBK + 1;
+  if (w < nkt) load_tile(w * kBK);
+  Op qop[KS];
+  load_query<P, KS, QM>(q, st, qi, T, L, c, qop);
+  float m = 0.0f, l = 0.0f, uii = 0.0f;
+  floatx16 oacc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) oacc[db] = floatx16{};
+
+  for (int kt0 = 0; kt0 < nkt; kt0 += NW) {  // every wave meets every barrier
+    const int kt = kt0 + w;
+    if (kt0 > 0) {
+      __syncthreads();  // the tiles before are read
+      if (kt < nkt) load_tile(kt * kBK);
+    }
+    wait_loads();
+    __syncthreads();
+    if (kt < nkt) {
+      if ((kt + 1) * kBK <= qr0) fast_keys64<P, D, QM, true>(Ks, Vs, 0, kt * kBK, qr0, qop, oacc, m, l, uii, L, c);
+      else fast_keys64<P, D, QM, false>(Ks, Vs, 0, kt * kBK, qr0, qop, oacc, m, l, uii, L, c);
+    }
+  }
+  __syncthreads();
+  float* zw = reinterpret_cast<float*>(tiles + w * 2 * TB);
+#pragma unroll
+  for (int x = 0; x < 4 * DB; ++x)
+    *reinterpret_cast<floatx4*>(zw + (x * 64 + lane) * 4) =
+        floatx4{oacc[x / 4][4 * (x % 4)], oacc[x / 4][4 * (x % 4) + 1], oacc[x / 4][4 * (x % 4) + 2],
+                oacc[x / 4][4 * (x % 4) + 3]};
+  lsh[w][lane] = l;
+  ush[w][lane] = uii;
+  __syncthreads();
+  l = (lsh[0][lane] + lsh[1][lane]) + (lsh[2][lane] + lsh[3][lane]);
+  uii = (ush[0][lane] + ush[1][lane]) + (ush[2][lane] + ush[3][lane]);  // one wave holds the diagonal, the rest 0
+  const float lt = l + xor32(l);
+  if (wave_any(qi < T && !(lt <= kSpecMax))) {
+    // the same in every wave; as in fwd_kernel the rows are scanned again with
+    // the rescaling loop, here by the first wave alone
+    m = l = uii = 0.0f;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[db] = floatx16{};
+    for (int kt = 0; kt < nkt; ++kt) {
+      __syncthreads();
+      if (w == 0) load_tile(kt * kBK);
+      wait_loads();
+      __syncthreads();
+      if (w == 0) slow_keys64<P, D, QM>(Ks, Vs, 0, kt * kBK, qr0, qop, oacc, m, l, uii, L, c);
+    }
+    if (w == 0) finish_row<P, D, QM>(a, o, v, st, head, qi, m, l, uii, oacc, L, c);
+    return;
+  }
+  const float u_other = xor32(uii);
+  float un = holds_row(L.n, L.g) ? uii : u_other;
+  if (QM == 0) un *= c;
+  if (qi >= T) return;
+  const float lam = *a.lambda;
+  const float ln_i = logf((float)(qi + 1));
+  const RowEpilogue e = row_epilogue(0.0f, lt, un, a.inv_tau, lam, ln_i);
+  const float wself = a.exch_only ? 0.0f : e.omg;
+#pragma unroll
+  for (int y = 0; y < DB; ++y) {
+    const int x = DB * w + y, d0 = 32 * (x / 4) + 8 * (x % 4) + 4 * L.g;
+    floatx4 z = {};
+#pragma unroll
+    for (int ow = 0; ow < NW; ++ow)
+      z += *reinterpret_cast<const floatx4*>(tiles + ow * 2 * TB + (x * 64 + lane) * 16);
+    const floatx4 vi = P::load4(v + qi * st + d0);
+    floatx4 out;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) out[t] = __builtin_fmaf(wself, vi[t], e.inv_l * z[t]);
+    P::store4(o + qi * st + d0, out);
+  }
+  if (w == 0) store_row_stats(a, head, qi, e, lam, ln_i, L);
+}
+
+// The number of 128-row workgroups up to which the rows go to 32-row ones. Both
+// times at the limit and past it (us, 128 against 32 rows), T >= 1024, where the
+// chain is long: D = 64 23.1 and 20.5 at 256, 24.2 and 29.4 at 384 (T = 1024);
+// where one 32-row workgroup fills a CU's LDS in bf16 D = 96 25.2 and 22.1 at
+// 128, 25.7 and 29.1 at 160; fp32 D = 64 159 and 123 at 256. Shorter: D = 64 10.2
+// and 8.6 at 128, 10.4 and 10.6 at 192 (T = 256); D = 96 11.5 and 13.1 at 128.
+template <class P, int D>
+int64_t few_tiles(int T) {
+  const int64_t most = sizeof(typename P::T) == 2 && D > 64 ? 128 : 256;
+  return T >= 1024 ? most : most / 2;
+}
+
+template <class P, int D>
+void launch_one(FwdArgs a, hipStream_t stream) {
+  if constexpr (2 * kNT / 64 * kBK * P::ROWB <= 131072) {  // the tiles of four waves fit the LDS (not fp32, D = 128)
+    if ((int64_t)a.map.N * ((a.T + kBQ - 1) / kBQ) <= few_tiles<P, D>(a.T)) {
+      a.map = make_tilemap(a.map.N, (a.T + 31) / 32);
+      hipLaunchKernelGGL((fwd_split_kernel<P, D>), dim3((unsigned)grid_size(a.map)), dim3(kNT), 0, stream, a);
+      return;
+    }
+  }
+  a.map = make_tilemap(a.map.N, (a.T + kBQ - 1) / kBQ);
   hipLaunchKernelGGL((fwd_kernel<P, D>), dim3((unsigned)grid_size(a.map)), dim3(kNT), 0, stream, a);
 }
 
 }  // namespace
 
 hipError_t launch_fwd(const FwdArgs& a0, int dtype, int D, hipStream_t stream) {
-  FwdArgs a = a0;
-  a.map = make_tilemap(a.map.N, (a.T + kBQ - 1) / kBQ);
+  const FwdArgs& a = a0;
   hipEvent_t ev0, ev1;
   const bool prof = profile_slot("fwd", &ev0, &ev1);
   if (prof) (void)hipEventRecord(ev0, stream);

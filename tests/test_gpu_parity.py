@@ -473,3 +473,34 @@ def test_autograd_lambda_forms_and_broadcast_gradient(lam_shape, lam_dtype, expa
         assert torch.allclose(got.float(), b[n].float(), rtol=2 ** -7, atol=2 ** -7), n  # dq's order of sums may differ
     assert grads[3].shape == lam.shape and grads[3].dtype == lam.dtype
     assert abs(float(grads[3]) - float(b["dlambda"])) <= 1e-4 * (1 + abs(float(b["dlambda"])))
+
+
+@pytest.mark.parametrize("B,H,T,D,dtype", [
+    (1, 1, 1, 64, "bf16"), (1, 2, 33, 32, "bf16"), (1, 3, 257, 64, "bf16"), (1, 2, 319, 96, "bf16"),
+    (1, 2, 290, 128, "bf16"), (1, 12, 65, 64, "bf16"), (2, 5, 130, 64, "bf16"), (1, 3, 100, 32, "f32"),
+    (1, 2, 321, 64, "f32"), (1, 1, 300, 128, "f32"),
+])
+def test_few_workgroups(B, H, T, D, dtype):
+    """Few workgroups: the forward shares a row block's keys among its waves (1
+    to 6 tiles for four waves, ragged ends), and the heads alternate over the
+    workgroups where their number leaves dies idle; forward, both backwards."""
+    x = _prep(I.make_inputs(B, H, T, D, seed=3000 + T + D, qkv_std=1.0 if dtype == "f32" else 1.0 / math.sqrt(D),
+                            with_dout=True), dtype)
+    f = check_forward(x, dtype)
+    check_backward(x, dtype, f)
+    check_backward(x, dtype, f, deterministic=True)
+
+
+@pytest.mark.parametrize("H,D,dtype", [(2, 64, "bf16"), (2, 128, "bf16"), (2, 32, "f32"), (130, 64, "bf16")])
+def test_rescan_few_and_many_workgroups(H, D, dtype):
+    """Rows whose weights pass the fixed reference's range are scanned again, in
+    the split forward (H = 2) and in the 128-row workgroups (H = 130); the other
+    rows of their blocks and the other blocks come along."""
+    x = _prep(I.make_inputs(1, H, 300, D, seed=3100 + D, qkv_std=0.5), dtype)
+    boost = torch.ones(300, 1, device="cuda")
+    boost[[40, 170, 290]] = 2.0 ** 8
+    x["q"] = (x["q"].float() * boost).to(x["q"].dtype)
+    x["qr"] = _np(x["q"])
+    out = check_forward(x, dtype, heads=[(0, 0), (0, H - 1)])
+    le = _np(out["exch_lse"])
+    assert np.nanmax(le[np.isfinite(le)]) > 64 * np.log(2), "inputs do not reach the rescan path"
