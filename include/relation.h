@@ -343,9 +343,11 @@ rel_status relation_decode_merge(const rel_problem* p, int32_t nstates, const fl
  *   state_out  [B,H,D,D] fp32, optional: C_T, the decode state after the last
  *              token (rows: relation channel, columns: information channel).
  *   workspace  relation_linear_fwd_workspace_bytes(p) bytes, 16-byte aligned:
- *              per chunk of 64 tokens its state contribution and retention
+ *              fp32, per chunk of 64 tokens its state contribution and retention
  *              product, and the state entering it; per segment of 16 chunks
- *              the scan's summary (fp32).
+ *              the scan's summary. bf16: per chunk the state entering it from a
+ *              zero start of its segment (1 to 8 chunks) and its retention, per
+ *              segment the result (all in 32 bits).
  * Precision: fp32 inputs run every product in fp32. bf16 inputs take the
  * chunk products on bf16 operands with fp32 accumulation, except that the
  * backward keeps fp32 accuracy in the products that reach dg (and so dr,
@@ -358,7 +360,7 @@ rel_status relation_linear_fwd(const rel_problem* p, const void* p1, const void*
 /* Linear Relation backward: gradients of sum(dout * y) with respect to p1,
  * p2, v (dtype, the problem's strides) and g (fp32, dense [B,H,T,D]). The
  * chunk states are recomputed from the inputs. D in {32, 64, 128}. At D = 128
- * the state is taken as four 64 x 64 blocks (halves of the relation and of
+ * with fp32 inputs the state is taken as four 64 x 64 blocks (halves of the relation and of
  * the information channels), each of which evolves on its own, and the
  * gradient is the sum of the four blocks' terms; the result matches the
  * one-block computation up to fp32 rounding order. Head widths between these
@@ -367,10 +369,12 @@ rel_status relation_linear_fwd(const rel_problem* p, const void* p1, const void*
  *   workspace  relation_linear_bwd_workspace_bytes(p) bytes, 16-byte aligned:
  *              the forward workspace plus, per chunk, the D x D products that
  *              the reverse scan over chunks reads and the state gradients it
- *              writes, and per segment of 16 chunks the reverse summary. At
- *              D = 128 the chunk states are those of 4 B H heads of width 64,
+ *              writes, and per segment the reverse summary. bf16 at D >= 64
+ *              adds one fp32 plane for channels of steep decay. fp32 at
+ *              D = 128: the chunk states are those of 4 B H heads of width 64,
  *              plus S ^p1 and S ^p2 of every row and eight fp32 [B,H,T,128]
- *              planes of partial gradients (5 KiB per token and head). */
+ *              planes of partial gradients (5 KiB per token and head). At
+ *              D = 128 the size is at least ten fp32 planes in both types. */
 size_t relation_linear_bwd_workspace_bytes(const rel_problem* p);
 rel_status relation_linear_bwd(const rel_problem* p, const void* p1, const void* p2, const void* v,
                                const float* g, const void* dout, void* dp1, void* dp2, void* dv, float* dg,
