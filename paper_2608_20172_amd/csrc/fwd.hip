@@ -572,10 +572,12 @@ __global__ __launch_bounds__(kNT, (fwd_split_occupancy<P, D>())) void fwd_split_
 // where one 32-row workgroup fills a CU's LDS in bf16 D = 96 25.2 and 22.1 at
 // 128, 25.7 and 29.1 at 160; fp32 D = 64 159 and 123 at 256. Shorter: D = 64 10.2
 // and 8.6 at 128, 10.4 and 10.6 at 192 (T = 256); D = 96 11.5 and 13.1 at 128.
+// Below 256 tokens a 128-row workgroup has one or two tiles: fp32 layers of 55 x 2
+// heads x 125 at D = 64 lost 2% with the split, D = 64 in bf16 7.8 and 7.4 at 128.
 template <class P, int D>
 int64_t few_tiles(int T) {
   const int64_t most = sizeof(typename P::T) == 2 && D > 64 ? 128 : 256;
-  return T >= 1024 ? most : most / 2;
+  return T >= 1024 ? most : T >= 256 ? most / 2 : most / 4;
 }
 
 template <class P, int D>
