@@ -190,7 +190,7 @@ struct LinearArgs {
   // from a zero start at the segment's edge; segc and segp the state entering
   // (the gradient leaving) each segment; gpre and gsuf [N, nchunks, D] the
   // retention of the segment's chunks before (after) the chunk.
-  int seg;
+  int seg;               // 0: linear.hip's kernels
   float* gpre;
   float* gsuf;
 };
@@ -219,7 +219,7 @@ hipError_t launch_linear_fwd(const LinearArgs& a, int dtype, hipStream_t stream)
 hipError_t launch_linear_bwd(const LinearArgs& a, int dtype, hipStream_t stream);
 // bf16 inputs (linear_bf16.hip): chunks per segment of its state kernel, and the passes.
 int linear_bf16_segment(int64_t heads, int nchunks);
-size_t linear_bf16_rope_bytes(int nchunks, int rope_dim);
+bool linear_bf16_route(int64_t heads, int nchunks, int D, bool gated, bool rope, bool backward);
 hipError_t launch_linear_bf16_rope_table(float2* tab, int nchunks, int rope_dim, double base, hipStream_t stream);
 hipError_t launch_linear_bf16_fwd(const LinearArgs& a, hipStream_t stream);
 hipError_t launch_linear_bf16_bwd(const LinearArgs& a, hipStream_t stream);

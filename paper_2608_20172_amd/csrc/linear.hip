@@ -1,5 +1,6 @@
-// Linear Relation (Sec. 5.2, App. A.4), fp32 inputs (linear_bf16.hip has the
-// bf16 kernels): Self stays explicit, Exchange reads a
+// Linear Relation (Sec. 5.2, App. A.4), for fp32 inputs and for bf16 problems of
+// few chunks (linear_bf16.hip has the other bf16 kernels and the rule,
+// linear_bf16_route): Self stays explicit, Exchange reads a
 // recurrent state C (D x D per head) with channel-wise retention alpha = exp(g).
 //   S_t = sigmoid(p1_t . p2_t / (tau_S sqrt(D))),  ^p = p / |p|
 //   C_t^- = Diag(alpha_t) C_{t-1};  Y_t = I~_t + S_t (C_t^-)^T ^p1_t;
@@ -13,12 +14,14 @@
 // Every exponent is <= 0 (g <= 0), so nothing overflows, whatever the decay.
 // Forward launches: per chunk the state contribution (dC, gamma = e^{b_last});
 // the scan over chunks in segments (the state entering every chunk); per chunk
-// the output. Dense products run on the matrix cores, the decay weights on the
-// vector units, and the diagonal sub-blocks of the intra-chunk pairs on the
-// matrix cores where the chunk's decay lets them be factored, else term by term
-// on the vector units. With the gated entry points the kernels also form g from
-// the KDA gate and rotate p1, p2 with RoPE as they load a chunk (and take both
-// back in the gradient).
+// the output. Dense products run on the matrix cores (fp32 MFMA for fp32
+// inputs; for bf16 inputs bf16 MFMA with fp32 accumulation, except in the
+// backward's products that reach the decay gradient), the decay weights on
+// the vector units in fp32, and the diagonal sub-blocks of the intra-chunk
+// pairs on the matrix cores where the chunk's decay lets them be factored,
+// else term by term on the vector units. With
+// the gated entry points the kernels also form g from the KDA gate and rotate
+// p1, p2 with RoPE as they load a chunk (and take both back in the gradient).
 #include "kernels.h"
 #include "lanes.h"
 
@@ -110,8 +113,18 @@ __device__ __forceinline__ int swz(int r, int c) {
   return (((c >> 2) ^ (r & (D / 4 - 1))) << 2) | (c & 3);
 }
 
-// 16 bytes of a row.
+// 16 bytes of a row (8 bf16 or 4 fp32 elements) as floats.
 template <typename TI> struct Vec16;
+template <> struct Vec16<bf16> {
+  static __device__ __forceinline__ void load(const bf16* p, float (&x)[8]) {
+    const uintx4 u = *reinterpret_cast<const uintx4*>(p);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      x[2 * t] = bf16_lo(u[t]);
+      x[2 * t + 1] = bf16_hi(u[t]);
+    }
+  }
+};
 template <> struct Vec16<float> {
   static __device__ __forceinline__ void load(const float* p, float (&x)[4]) {
     const float4 u = *reinterpret_cast<const float4*>(p);
@@ -119,9 +132,22 @@ template <> struct Vec16<float> {
   }
 };
 
-// 4 consecutive elements, for rows that start on 16-byte boundaries and
-// offsets that are multiples of 4.
+// 4 consecutive elements (8 bytes of bf16, 16 of fp32), for rows that start
+// on 16-byte boundaries and offsets that are multiples of 4.
 template <typename TI> struct Vec4;
+template <> struct Vec4<bf16> {
+  static __device__ __forceinline__ void load(const bf16* p, float (&x)[4]) {
+    const uint2 u = *reinterpret_cast<const uint2*>(p);
+    x[0] = bf16_lo(u.x); x[1] = bf16_hi(u.x); x[2] = bf16_lo(u.y); x[3] = bf16_hi(u.y);
+  }
+  static __device__ __forceinline__ void store(bf16* p, const float (&x)[4]) {
+    typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    bf16x4 o;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) o[t] = (bf16)x[t];
+    *reinterpret_cast<bf16x4*>(p) = o;
+  }
+};
 template <> struct Vec4<float> {
   static __device__ __forceinline__ void load(const float* p, float (&x)[4]) {
     const float4 u = *reinterpret_cast<const float4*>(p);
@@ -342,19 +368,108 @@ __device__ __forceinline__ void load_chunk(const LinearArgs& a, const ChunkPos& 
   __syncthreads();
 }
 
+// Matrix-core operands. With fp32 inputs every product runs on fp32 MFMA
+// steps. With bf16 inputs (BF) the operands, formed in fp32, are rounded to
+// bf16 and the products run on bf16 MFMA steps with fp32 accumulation, eight
+// fp32 steps' worth of contraction per instruction. A lane supplies the values
+// of its row of the left operand and of its column of the right operand at the
+// same contraction indices; which indices go to which lane and slot does not
+// matter to the sum, so each lane keeps the index range it has on the fp32 path.
+// The backward keeps fp32 accuracy in every product that reaches the
+// gradient of the decay (dq, dk, and the states C0 and G): fp32 steps, or,
+// where one operand is a bf16 input, bf16 steps with the other split in three
+// bf16 parts (exact products). That gradient is a small difference of large
+// terms (the scores depend on b only through b_t - b_j, so the intra-chunk
+// parts of qt dq and kt dk cancel over a chunk), and operands rounded to bf16
+// leave a residual of their rounding in it that adds up coherently over the
+// tokens in dA_log.
+template <typename TI> constexpr bool kBF = sizeof(TI) == 2;
+
+template <int N>
+__device__ __forceinline__ void pack_bf16(const float* x, __bf16 __attribute__((ext_vector_type(N))) & o) {
+#pragma unroll
+  for (int t = 0; t < N; ++t) o[t] = (bf16)x[t];
+}
+__device__ __forceinline__ floatx4 mfma16b(const float (&a)[8], const float (&b)[8], const floatx4& c) {
+  bf16x8 x, y;
+  pack_bf16<8>(a, x);
+  pack_bf16<8>(b, y);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 mfma16b4(const float (&a)[4], const float (&b)[4], const floatx4& c) {
+  bf16x4 x, y;
+  pack_bf16<4>(a, x);
+  pack_bf16<4>(b, y);
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(shortx4, x), __builtin_bit_cast(shortx4, y), c,
+                                                   0, 0, 0);
+}
+__device__ __forceinline__ floatx16 mfma32b(const float (&a)[8], const float (&b)[8], const floatx16& c) {
+  bf16x8 x, y;
+  pack_bf16<8>(a, x);
+  pack_bf16<8>(b, y);
+  return mfma32(x, y, c);
+}
+
 // One 32 x 32 block (rows ab.., columns eb..) of X^T Y, the contraction over
 // the kL rows of the chunk (X, Y plain [kL][D] arrays), on the matrix cores
-// (32x32x2 steps; lane group g takes the rows of parity g).
-template <int D>
+// (lane group g takes the rows of parity g: 32x32x2 fp32 steps, or 32x32x16
+// bf16 steps of eight such rows with BF).
+template <int D, bool BF = false>
 __device__ __forceinline__ floatx16 gram_block(const float (*X)[D], const float (*Y)[D], int ab, int eb) {
   const int lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
   floatx16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+  if constexpr (BF) {
+#pragma unroll
+    for (int s = 0; s < kL / 16; ++s) {
+      float x[8], y[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int r = 16 * s + 2 * u + lg;
+        x[u] = X[r][ab + ln];
+        y[u] = Y[r][eb + ln];
+      }
+      acc = mfma32b(x, y, acc);
+    }
+  } else {
 #pragma unroll 8
-  for (int s2 = 0; s2 < kL / 2; ++s2) {
-    const int r = 2 * s2 + lg;
-    acc = mfma32f(X[r][ab + ln], Y[r][eb + ln], acc);
+    for (int s2 = 0; s2 < kL / 2; ++s2) {
+      const int r = 2 * s2 + lg;
+      acc = mfma32f(X[r][ab + ln], Y[r][eb + ln], acc);
+    }
+  }
+  return acc;
+}
+
+// gram_block for a right operand Y whose values are bf16 numbers (the bf16
+// inputs, held in fp32): X is split as hi + mid + lo, three bf16 numbers that
+// carry its 24 significant bits, so the three 32x32x16 bf16 steps per 16 rows
+// give exact products with fp32 accumulation, as the fp32 steps would.
+template <int D>
+__device__ __forceinline__ floatx16 gram_block_split3(const float (*X)[D], const float (*Y)[D], int ab, int eb) {
+  const int lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
+  floatx16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+#pragma unroll 1
+  for (int s = 0; s < kL / 16; ++s) {
+    bf16x8 hv, mv, lv, yv;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int r = 16 * s + 2 * u + lg;
+      const float x = X[r][ab + ln];
+      const bf16 h = (bf16)x;
+      const float r1 = x - (float)h;
+      const bf16 m = (bf16)r1;
+      hv[u] = h;
+      mv[u] = m;
+      lv[u] = (bf16)(r1 - (float)m);
+      yv[u] = (bf16)Y[r][eb + ln];
+    }
+    acc = mfma32(hv, yv, acc);
+    acc = mfma32(mv, yv, acc);
+    acc = mfma32(lv, yv, acc);
   }
   return acc;
 }
@@ -386,7 +501,7 @@ __global__ __launch_bounds__(kLT) void linear_state_kernel(LinearArgs a) {
   constexpr int NBE = D / 32;
   for (int bk = __builtin_amdgcn_readfirstlane(tid >> 6); bk < NBE * NBE; bk += kLT / 64) {
     const int ab = 32 * (bk / NBE), eb = 32 * (bk % NBE);
-    store_block<D>(a.dstate + base * D * D, gram_block<D>(kt, vv, ab, eb), ab, eb);
+    store_block<D>(a.dstate + base * D * D, gram_block<D, kBF<TI>>(kt, vv, ab, eb), ab, eb);
   }
 }
 
@@ -498,21 +613,81 @@ hipError_t launch_state_scan(const LinearArgs& a, int reverse, hipStream_t strea
 }
 
 // acc += one 32 x 32 block (rows rb.., columns cb..) of a product X B whose
-// contraction runs over the K columns of X, on the matrix cores (32x32x2
-// steps). X is a swizzled (swz) row-major [kL][K] array; B(k, j) gives the
-// column operand. Lane group g takes the contraction indices K/2 g .. K/2 g +
-// K/2 - 1 in order, four per 16-byte read of its row of X.
-template <int K, typename ColOp>
+// contraction runs over the K columns of X, on the matrix cores (32x32x2 fp32
+// steps, or 32x32x16 bf16 steps with BF). X is a swizzled (swz) row-major
+// [kL][K] array; B(k, j) gives the column operand. Lane group g takes the
+// contraction indices K/2 g .. K/2 g + K/2 - 1 in order, four per 16-byte read
+// of its row of X.
+template <int K, bool BF = false, typename ColOp>
 __device__ __forceinline__ floatx16 block_product(const float (*X)[K], int rb, int cb, floatx16 acc, ColOp B) {
   constexpr int KH = K / 2;
   const int lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
   const int xr = rb + ln;
+  if constexpr (BF) {
+    static_assert(KH % 8 == 0, "whole bf16 steps");
 #pragma unroll 2
-  for (int s0 = 0; s0 < KH; s0 += 4) {
-    const int kk = KH * lg + s0;
-    const floatx4 xa = *reinterpret_cast<const floatx4*>(&X[xr][swz<K>(xr, kk)]);
+    for (int s0 = 0; s0 < KH; s0 += 8) {
+      const int kk = KH * lg + s0;
+      const floatx4 x0 = *reinterpret_cast<const floatx4*>(&X[xr][swz<K>(xr, kk)]);
+      const floatx4 x1 = *reinterpret_cast<const floatx4*>(&X[xr][swz<K>(xr, kk + 4)]);
+      float xa[8], xb[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc = mfma32f(xa[u], B(kk + u, cb + ln), acc);
+      for (int u = 0; u < 4; ++u) {
+        xa[u] = x0[u];
+        xa[4 + u] = x1[u];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) xb[u] = B(kk + u, cb + ln);
+      acc = mfma32b(xa, xb, acc);
+    }
+  } else {
+#pragma unroll 2
+    for (int s0 = 0; s0 < KH; s0 += 4) {
+      const int kk = KH * lg + s0;
+      const floatx4 xa = *reinterpret_cast<const floatx4*>(&X[xr][swz<K>(xr, kk)]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = mfma32f(xa[u], B(kk + u, cb + ln), acc);
+    }
+  }
+  return acc;
+}
+
+// acc += one 32 x 32 block of X B as block_product, for a row operand X whose
+// values are bf16 numbers (the bf16 inputs, held in fp32) and any fp32 column
+// operand: B is split as b = hi + mid + lo, three bf16 numbers that carry its
+// 24 significant bits, and the block takes three 32x32x16 bf16 steps per 16
+// contraction indices, with the products exact and fp32 accumulation, where
+// fp32 steps take eight.
+template <int K, typename ColOp>
+__device__ __forceinline__ floatx16 block_product_split3(const float (*X)[K], int rb, int cb, floatx16 acc, ColOp B) {
+  constexpr int KH = K / 2;
+  static_assert(KH % 8 == 0, "whole bf16 steps");
+  const int lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
+  const int xr = rb + ln;
+#pragma unroll 1
+  for (int s0 = 0; s0 < KH; s0 += 8) {
+    const int kk = KH * lg + s0;
+    const floatx4 x0 = *reinterpret_cast<const floatx4*>(&X[xr][swz<K>(xr, kk)]);
+    const floatx4 x1 = *reinterpret_cast<const floatx4*>(&X[xr][swz<K>(xr, kk + 4)]);
+    bf16x8 xv, hv, mv, lv;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      xv[u] = (bf16)x0[u];
+      xv[4 + u] = (bf16)x1[u];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float b = B(kk + u, cb + ln);
+      const bf16 h = (bf16)b;
+      const float r1 = b - (float)h;
+      const bf16 m = (bf16)r1;
+      hv[u] = h;
+      mv[u] = m;
+      lv[u] = (bf16)(r1 - (float)m);
+    }
+    acc = mfma32(xv, hv, acc);
+    acc = mfma32(xv, mv, acc);
+    acc = mfma32(xv, lv, acc);
   }
   return acc;
 }
@@ -567,7 +742,7 @@ __device__ __forceinline__ bool diag_factorable(const float (*bb)[D]) {
 // j >= t set to zero; otherwise it is summed term by term on the vector units.
 // Waves 0-3 of the workgroup: diagonal block w; waves 4-7: blocks w - 4 and w
 // (of the six below the diagonal). With TRANS the scores go to A as A^T (A[j][t]).
-template <int D>
+template <int D, bool BF = false>
 __device__ __forceinline__ floatx4 scaled_block(const float (*qt)[D], const float (*kt)[D], const float (*bb)[D],
                                                 int tb, int jb, int rf) {
   constexpr int CH = D / 4;
@@ -585,17 +760,28 @@ __device__ __forceinline__ floatx4 scaled_block(const float (*qt)[D], const floa
     }
   };
   // lane group g takes the channel chunks CH/4 g .. CH/4 g + CH/4 - 1
+  if constexpr (BF) {
+    static_assert(CH % 8 == 0, "two chunks per bf16 step");
 #pragma unroll 2
-  for (int c0 = 0; c0 < CH / 4; ++c0) {
-    float qa[4], kb[4];
-    operands((CH / 4) * g + c0, qa, kb);
+    for (int c0 = 0; c0 < CH / 4; c0 += 2) {
+      float qa[8], kb[8];
+      operands((CH / 4) * g + c0, qa, kb);
+      operands((CH / 4) * g + c0 + 1, qa + 4, kb + 4);
+      acc = mfma16b(qa, kb, acc);
+    }
+  } else {
+#pragma unroll 2
+    for (int c0 = 0; c0 < CH / 4; ++c0) {
+      float qa[4], kb[4];
+      operands((CH / 4) * g + c0, qa, kb);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc = mfma16f(qa[u], kb[u], acc);
+      for (int u = 0; u < 4; ++u) acc = mfma16f(qa[u], kb[u], acc);
+    }
   }
   return acc;
 }
 
-template <int D, bool TRANS = false>
+template <int D, bool TRANS = false, bool BF = false>
 __device__ __forceinline__ void chunk_scores(const float (*qt)[D], const float (*kt)[D], const float (*bb)[D],
                                              float (*A)[kL], bool fact) {
   constexpr int SB = 16, NSB = kL / SB, CH = D / 4;
@@ -607,7 +793,7 @@ __device__ __forceinline__ void chunk_scores(const float (*qt)[D], const float (
   };
   if (w < NSB && fact) {
     const int i = lane & 15, g = lane >> 4;
-    const floatx4 acc = scaled_block<D>(qt, kt, bb, w, w, SB * w);
+    const floatx4 acc = scaled_block<D, BF>(qt, kt, bb, w, w, SB * w);
 #pragma unroll
     for (int v = 0; v < 4; ++v) put(SB * w + 4 * g + v, SB * w + i, i < 4 * g + v ? acc[v] : 0.0f);
     for (int jb = w + 1; jb < NSB; ++jb) {  // the blocks above the diagonal in the row band are zero
@@ -662,7 +848,7 @@ __device__ __forceinline__ void chunk_scores(const float (*qt)[D], const float (
       // blocks below the diagonal, bi = 0..5: (1,0) (2,0) (3,0) (2,1) (3,1) (3,2)
       const int jb = bi < 3 ? 0 : bi < 5 ? 1 : 2;
       const int tb = jb + 1 + (bi < 3 ? bi : bi < 5 ? bi - 3 : 0);
-      const floatx4 acc = scaled_block<D>(qt, kt, bb, tb, jb, SB * jb + SB - 1);
+      const floatx4 acc = scaled_block<D, BF>(qt, kt, bb, tb, jb, SB * jb + SB - 1);
       // register v of lane (i, g): row 4 g + v, column i of the block
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
@@ -695,7 +881,7 @@ __global__ __launch_bounds__(kLT2) void linear_out_kernel(LinearArgs a) {
     for (int k = 0; k < NC0; ++k) c0r[k] = C0[tid + k * kLT2];
   }
   load_chunk<TI, D, kLT2, false, false, true>(a, p, qt, kt, vv, bb, nullptr);
-  chunk_scores<D, false>(qt, kt, bb, A, diag_factorable<D>(bb));
+  chunk_scores<D, false, kBF<TI>>(qt, kt, bb, A, diag_factorable<D>(bb));
   __syncthreads();
   // Qe = qt e^{b} (the inter read's query), over kt; all three swizzled alike
   for (int i = tid; i < kL * D; i += kLT2) {
@@ -722,9 +908,9 @@ __global__ __launch_bounds__(kLT2) void linear_out_kernel(LinearArgs a) {
   const int rb = 32 * (blk / NBC), cb = 32 * (blk % NBC);
   const bool busy = w < (SPLIT ? 2 * NB : NB);
   floatx16 acc = zero16();
-  if (busy && part == 0) acc = block_product<kL>(A, rb, cb, acc, [&](int k, int j) { return vv[k][j]; });
+  if (busy && part == 0) acc = block_product<kL, kBF<TI>>(A, rb, cb, acc, [&](int k, int j) { return vv[k][j]; });
   if (busy && (!SPLIT || part == 1))
-    acc = block_product<D>(kt, rb, cb, acc, [&](int k, int j) { return C0s[k * D + j]; });
+    acc = block_product<D, kBF<TI>>(kt, rb, cb, acc, [&](int k, int j) { return C0s[k * D + j]; });
   float* Ap = &A[0][0];
   if constexpr (SPLIT) {
     __syncthreads();  // every operand of A read
@@ -782,26 +968,59 @@ __global__ __launch_bounds__(kLT) void linear_bstate_kernel(LinearArgs a) {
   constexpr int NBE = D / 32, NBB = NBE * NBE;
   for (int bk = __builtin_amdgcn_readfirstlane(tid >> 6); bk < 2 * NBB; bk += kLT / 64) {
     const int ab = 32 * ((bk % NBB) / NBE), eb = 32 * (bk % NBE);
-    const floatx16 acc = bk < NBB ? gram_block<D>(kt, vv, ab, eb) : gram_block<D>(qt, dy, ab, eb);
+    // C0 and G reach the decay gradient: fp32 steps, or with bf16 inputs
+    // (v and dY exact in bf16) bf16 steps on Kd and Qe split in three
+    floatx16 acc;
+    if constexpr (kBF<TI>) acc = bk < NBB ? gram_block_split3<D>(kt, vv, ab, eb) : gram_block_split3<D>(qt, dy, ab, eb);
+    else acc = bk < NBB ? gram_block<D>(kt, vv, ab, eb) : gram_block<D>(qt, dy, ab, eb);
     store_block<D>((bk < NBB ? a.dstate : a.pstate) + base * D * D, acc, ab, eb);
   }
 }
 
-// One 16 x 16 tile of a product on the matrix cores (16x16x4 steps):
+// One 16 x 16 tile of a product on the matrix cores (16x16x4 fp32 steps; with
+// BF, 16x16x32 bf16 steps and a 16x16x16 one for a remainder of four indices):
 // acc[v] of lane (i, g) = sum over k in [k0, k0 + K) of X[r0 + i][k] B(k, c0 + ...)
 // for output row r0 + 4 g + v and column c0 + i. X is a swizzled [kL][W]
 // array; B(k, j) gives the column operand. K is a multiple of 16 and k0 of 4;
 // lane group g takes the indices k0 + K/4 g .. k0 + K/4 g + K/4 - 1.
-template <int W, typename ColOp>
+template <int W, bool BF = false, typename ColOp>
 __device__ __forceinline__ floatx4 tile_product(const float (*X)[W], int r0, int c0, int k0, int K, ColOp B) {
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
   const int kq = K >> 2, xr = r0 + i;
   floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int s0 = 0; s0 < kq; s0 += 4) {
-    const int k = k0 + kq * g + s0;
-    const floatx4 xa = ld4<W>(X, xr, k >> 2);
+  if constexpr (BF) {
+    int s0 = 0;
+    for (; s0 + 8 <= kq; s0 += 8) {
+      const int k = k0 + kq * g + s0;
+      const floatx4 x0 = ld4<W>(X, xr, k >> 2), x1 = ld4<W>(X, xr, (k >> 2) + 1);
+      float xa[8], xb[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc = mfma16f(xa[u], B(k + u, c0 + i), acc);
+      for (int u = 0; u < 4; ++u) {
+        xa[u] = x0[u];
+        xa[4 + u] = x1[u];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) xb[u] = B(k + u, c0 + i);
+      acc = mfma16b(xa, xb, acc);
+    }
+    if (s0 < kq) {  // four indices left (K / 4 is a multiple of 4)
+      const int k = k0 + kq * g + s0;
+      const floatx4 x0 = ld4<W>(X, xr, k >> 2);
+      float xa[4], xb[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        xa[u] = x0[u];
+        xb[u] = B(k + u, c0 + i);
+      }
+      acc = mfma16b4(xa, xb, acc);
+    }
+  } else {
+    for (int s0 = 0; s0 < kq; s0 += 4) {
+      const int k = k0 + kq * g + s0;
+      const floatx4 xa = ld4<W>(X, xr, k >> 2);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = mfma16f(xa[u], B(k + u, c0 + i), acc);
+    }
   }
   return acc;
 }
@@ -865,7 +1084,7 @@ __global__ __launch_bounds__(kLTG) void linear_grad_kernel(LinearArgs a) {
   const bool fact = diag_factorable<D>(bb);
   // ---- scores and dA: waves 0-7 the scores (to M0 as A^T), waves 8-15 dA
   if (w < 8) {
-    chunk_scores<D, true>(qt, kt, bb, M0, fact);
+    chunk_scores<D, true, kBF<TI>>(qt, kt, bb, M0, fact);
   } else {
     // the ten blocks (tb, jb) with jb <= tb; wave 8 + i takes blocks i and i + 8
     const int i = lane & 15, g = lane >> 4;
@@ -875,7 +1094,7 @@ __global__ __launch_bounds__(kLTG) void linear_grad_kernel(LinearArgs a) {
         jb -= tb + 1;
         ++tb;
       }
-      const floatx4 acc = tile_product<D>(dy, SB * tb, SB * jb, 0, D, [&](int k, int j) { return vv[j][swz<D>(j, k)]; });
+      const floatx4 acc = tile_product<D, kBF<TI>>(dy, SB * tb, SB * jb, 0, D, [&](int k, int j) { return vv[j][swz<D>(j, k)]; });
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int t = SB * tb + 4 * g + v, j = SB * jb + i;
@@ -893,6 +1112,7 @@ __global__ __launch_bounds__(kLTG) void linear_grad_kernel(LinearArgs a) {
   //   type 2 (3 NE, 4 NE with FACT): dk_intra[j][d] = e^{b_rf - b_j} sum_t dA^T[j][t] qt[t][d] e^{b_t - b_rf},
   //     rf = 16 jb + 15, over t > rf or t >= 16 jb (FACT)
   // dA is zero for j >= t, so the diagonal blocks' upper triangles add nothing.
+  // Types 1 and 2 reach the decay gradient: fp32 steps at any input type.
   constexpr int NT0 = NSB * NE, NTT = NT0 + 2 * NSB * NE;
   constexpr int MAXT = (NTT + 15) / 16;
   const int nt1 = fact ? NSB * NE : (NSB - 1) * NE, tb1 = fact ? 0 : 1;
@@ -904,7 +1124,7 @@ __global__ __launch_bounds__(kLTG) void linear_grad_kernel(LinearArgs a) {
     res[m] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     if (tau < NT0) {
       const int jb = tau / NE, eb = tau % NE;
-      res[m] = tile_product<kL>(M0, SB * jb, SB * eb, SB * jb, kL - SB * jb,
+      res[m] = tile_product<kL, kBF<TI>>(M0, SB * jb, SB * eb, SB * jb, kL - SB * jb,
                                 [&](int k, int e) { return dy[k][swz<D>(k, e)]; });
     } else if (tau < NT0 + nt1) {
       const int tb = tb1 + (tau - NT0) / NE, db = (tau - NT0) % NE;
@@ -1057,14 +1277,19 @@ __global__ __launch_bounds__(kLTG) void linear_grad_kernel(LinearArgs a) {
   const int prod = w / NB, blk = w % NB;
   const int rb = 32 * (blk / NBC), cb = 32 * (blk % NBC);
   floatx16 acc;
+  // dQe and dKd reach the decay gradient: fp32 steps, or with bf16 inputs
+  // (dY and v exact in bf16) bf16 steps on C0 and G split in three, which
+  // give the fp32 products
   auto c0t = [&](int k, int j) { return C0s[j][k]; };
   auto gt = [&](int k, int j) { return Gs[j][swz<D>(j, k)]; };
   if (prod == 0) {
-    acc = block_product<D>(dy, rb, cb, zero16(), c0t);
+    if constexpr (kBF<TI>) acc = block_product_split3<D>(dy, rb, cb, zero16(), c0t);
+    else acc = block_product<D>(dy, rb, cb, zero16(), c0t);
   } else if (prod == 1) {
-    acc = block_product<D>(vv, rb, cb, zero16(), gt);
+    if constexpr (kBF<TI>) acc = block_product_split3<D>(vv, rb, cb, zero16(), gt);
+    else acc = block_product<D>(vv, rb, cb, zero16(), gt);
   } else if (prod == 2) {
-    acc = block_product<D>(Kd, rb, cb, zero16(), [&](int k, int j) { return Gs[k][swz<D>(k, j)]; });
+    acc = block_product<D, kBF<TI>>(Kd, rb, cb, zero16(), [&](int k, int j) { return Gs[k][swz<D>(k, j)]; });
   }
   __syncthreads();  // every operand read: dy, vv, M2 take the three results (plain)
   float(*Dx)[D] = reinterpret_cast<float(*)[D]>(&M2[0][0]);
@@ -1552,8 +1777,8 @@ __global__ __launch_bounds__(256) void linear_gate_reduce_kernel(LinearArgs a, i
   }
 }
 
-// The gradient kernels form dr and per-chunk sums themselves; the fp32
-// width-128 backward (its dg comes from the combine pass) takes the row pass.
+// The gradient kernels form dr and per-chunk sums themselves; the width-128
+// backward of this file (its dg comes from the combine pass) takes the row pass.
 hipError_t launch_gate_bwd(const LinearArgs& a, bool row_pass, hipStream_t stream) {
   int nseg = a.nchunks;
   if (row_pass) {
@@ -1626,13 +1851,15 @@ hipError_t launch_linear_rope_table(float2* tab, int T, int rope_dim, double bas
 int linear_scan_segment() { return kSegChunks; }
 
 hipError_t launch_linear_fwd(const LinearArgs& a, int dtype, hipStream_t stream) {
-  return dtype == 1 ? launch_linear_bf16_fwd(a, stream) : launch_fwd_t<float>(a, stream);
+  if (a.seg) return launch_linear_bf16_fwd(a, stream);
+  return dtype == 1 ? launch_fwd_t<bf16>(a, stream) : launch_fwd_t<float>(a, stream);
 }
 
 hipError_t launch_linear_bwd(const LinearArgs& a, int dtype, hipStream_t stream) {
-  const hipError_t e = dtype == 1 ? launch_linear_bf16_bwd(a, stream) : launch_bwd_t<float>(a, stream);
+  const hipError_t e = a.seg ? launch_linear_bf16_bwd(a, stream)
+                       : dtype == 1 ? launch_bwd_t<bf16>(a, stream) : launch_bwd_t<float>(a, stream);
   if (e != hipSuccess || !a.a_log) return e;
-  return launch_gate_bwd(a, dtype == 0 && a.D == 128, stream);
+  return launch_gate_bwd(a, a.D == 128 && !a.seg, stream);
 }
 
 int linear_gate_segment() { return kGateSeg; }

@@ -1609,8 +1609,22 @@ int linear_bf16_segment(int64_t heads, int nchunks) {
   return s;
 }
 
-size_t linear_bf16_rope_bytes(int nchunks, int rope_dim) {
-  return (size_t)(nchunks + kL) * (size_t)rope_width(rope_dim / 2) * sizeof(float2);
+// Which bf16 problems this file's kernels take; linear.hip's take the rest.
+// Theirs share a chunk among more waves and scan up to 16 chunks a head in one
+// launch; with few chunks in all that shorter chain is the whole time. The gate
+// costs their width-128 backward a row pass, and RoPE costs them barriers.
+// Measured (us, linear.hip against this file; backward: with the forward):
+// width 128 backward 53 and 81 at 4 chunks, 63 and 95 at 32, 105 and 115 at 128,
+// 172 and 133 at 256; gated 75 and 90 at 4, 91 and 97 at 32, 109 and 104 at 32 (16
+// a head), 152 and 125 at 128. Width 128 forward 21 and 24 at 4, 31.6 and 34.7 at
+// 256, 28.2 and 28.0 with 32 a head; with RoPE 31 and 30 at 4, 41.5 and 43.1 at
+// 256. Width 64 backward 48 and 52 at 128, 51.6 and 55.9 at 256, 81 and 72 at 512,
+// 60 and 56 with 32 a head; with RoPE 65 and 65 at 128. Width 32: no slower here.
+bool linear_bf16_route(int64_t heads, int nchunks, int D, bool gated, bool rope, bool backward) {
+  const int64_t chunks = heads * nchunks;
+  if (D == 128 && backward) return chunks > (gated ? 32 : 160);
+  if (D < (backward ? 64 : 128) || rope) return true;
+  return nchunks > 16 || chunks > 256;
 }
 
 hipError_t launch_linear_bf16_rope_table(float2* tab, int nchunks, int rope_dim, double base, hipStream_t stream) {

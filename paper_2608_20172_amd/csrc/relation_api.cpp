@@ -1230,7 +1230,7 @@ struct LinearPlan {
   int seg, nseg;                                   // bf16: chunks per segment, segments
 };
 
-static bool linear_split(const rel_problem* p) { return p->D == 128 && p->dtype == REL_F32; }
+static bool linear_split(const rel_problem* p) { return p->D == 128; }
 
 static LinearPlan plan_linear_bf16(const rel_problem* p) {
   LinearPlan L{};
@@ -1249,15 +1249,14 @@ static LinearPlan plan_linear_bf16(const rel_problem* p) {
   L.gsuf = L.gout + states;
   L.qn = L.gsuf + rows;
   L.total_bwd = L.qn + (D >= 64 ? align256(N * (size_t)p->T * D * 4) : 0);
-  // width 128 promises its callers ten fp32 planes of the inputs' size; the layout above fits in them
-  if (D == 128) L.total_bwd = std::max(L.total_bwd, 10 * align256(N * (size_t)p->T * D * 4));
   L.gpart = L.total_bwd;
   L.total_gated = L.gpart + align256(N * nc * 2 * D * 4);
   return L;
 }
 
+// The plan of linear.hip's kernels. It needs at least what the bf16 plan needs,
+// so every workspace query and check takes its size.
 static LinearPlan plan_linear(const rel_problem* p, bool split) {
-  if (p->dtype == REL_BF16) return plan_linear_bf16(p);
   LinearPlan L{};
   const size_t N = (size_t)(p->B * p->H) * (split ? 4 : 1), nc = (size_t)linear_chunks(p);
   const size_t D = split ? (size_t)p->D / 2 : (size_t)p->D;
@@ -1343,8 +1342,13 @@ static rel_status check_rope(const rel_problem* p, int32_t rope_dim, float rope_
   return REL_OK;
 }
 
+// Whether linear_bf16.hip's kernels take the problem.
+static bool linear_bf16(const rel_problem* p, bool gated, bool rope, bool backward) {
+  return p->dtype == REL_BF16 &&
+         rel::linear_bf16_route(p->B * p->H, linear_chunks(p), (int)p->D, gated, rope, backward);
+}
+
 static size_t rope_table_bytes(const rel_problem* p, int32_t rope_dim) {
-  if (rope_dim > 0 && p->dtype == REL_BF16) return align256(rel::linear_bf16_rope_bytes(linear_chunks(p), rope_dim));
   const size_t rows = (size_t)linear_chunks(p) + (size_t)rel::linear_chunk();
   return rope_dim > 0 ? align256(rows * (size_t)(rope_dim / 2) * 8) : 0;
 }
@@ -1362,7 +1366,7 @@ static rel_status set_rope(rel::LinearArgs& a, const rel_problem* p, int32_t rop
   if (rope_dim == 0) return REL_OK;
   float2* tab = (float2*)(ws + off);
   const hipError_t e =
-      p->dtype == REL_BF16
+      a.seg
           ? rel::launch_linear_bf16_rope_table(tab, linear_chunks(p), (int)rope_dim, (double)rope_base, stream)
           : rel::launch_linear_rope_table(tab, (int)p->T, (int)rope_dim, (double)rope_base, stream);
   if (e != hipSuccess) return hip_fail(e, "RoPE table launch");
@@ -1419,8 +1423,9 @@ static rel_status linear_fwd_impl(const rel_problem* p, const void* p1, const vo
   a.nchunks = linear_chunks(p);
   a.nseg = linear_segments(p);
   a.vec16 = linear_vec16(p, {p1, p2, v, a_log, dt_bias}, g);
-  set_linear_workspace(a, L, (char*)workspace, false);
-  REL_TRY(set_rope(a, p, rope_dim, rope_base, (char*)workspace, L.total, (hipStream_t)stream));
+  const LinearPlan W = linear_bf16(p, a_log != nullptr, rope_dim > 0, false) ? plan_linear_bf16(p) : L;
+  set_linear_workspace(a, W, (char*)workspace, false);
+  REL_TRY(set_rope(a, p, rope_dim, rope_base, (char*)workspace, W.total, (hipStream_t)stream));
   const hipError_t e = rel::launch_linear_fwd(a, p->dtype, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "Linear Relation launch");
   return REL_OK;
@@ -1505,7 +1510,7 @@ static rel_status linear_bwd_impl(const rel_problem* p, const void* p1, const vo
                             {ddt_bias, pb, false, true, "ddt_bias"},
                             {workspace, need, false, true, "workspace"}}));
   if (test_fail_launch()) return fail(REL_ERR_HIP, "launch failure injected by RELATION_TEST_FAIL_LAUNCH");
-  const LinearPlan L = plan_linear(p, linear_split(p));
+  const LinearPlan L = linear_bf16(p, gated, rope_dim > 0, true) ? plan_linear_bf16(p) : plan_linear(p, linear_split(p));
   rel::LinearArgs a{};
   a.p1 = p1; a.p2 = p2; a.v = v; a.g = g; a.dy = dout;
   a.dp1 = dp1; a.dp2 = dp2; a.dv = dv; a.dg = dg;

@@ -401,6 +401,9 @@ def test_linear_gated_rope(width, padded, T, dtype):
 @pytest.mark.parametrize("H,T,D,steep", [
     (2, 15, 64, True), (2, 16, 32, False), (2, 63, 128, True), (2, 81, 64, True), (2, 16 * 64 + 1, 32, True),
     (64, 17 * 64 - 3, 64, True), (64, 17 * 64 + 16, 128, False), (72, 57 * 64 + 1, 32, True),
+    # both sides of the line between the two files' kernels, by chunks in all and per head
+    (16, 16 * 64 - 5, 64, True), (17, 16 * 64, 64, True), (2, 16 * 64 + 2, 64, True), (10, 16 * 64 - 3, 128, True),
+    (11, 15 * 64, 128, True),
 ])
 def test_linear_bf16_blocks_and_segments(H, T, D, steep):
     """The bf16 kernels at the edges of their 16-token blocks and 64-token
