@@ -408,8 +408,9 @@ def test_linear_gated_rope(width, padded, T, dtype):
 def test_linear_bf16_blocks_and_segments(H, T, D, steep):
     """The bf16 kernels at the edges of their 16-token blocks and 64-token
     chunks, and with segments of 1 (up to 16 and more of them), 2 and 8 chunks
-    whose last one is ragged, forward and backward, the first and the last head
-    against the oracle. steep: in every second chunk some channels (single ones
+    whose last one is ragged, and both sides of the rule that hands problems of
+    few chunks to the kernels shared with fp32, forward and backward, the first
+    and the last head against the oracle. steep: in every second chunk some channels (single ones
     and a run of eight) decay by up to e^-20 per token, past the range that the
     products' reference points cover, and the others stay slow.
 
