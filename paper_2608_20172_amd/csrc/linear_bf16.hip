@@ -541,9 +541,9 @@ __device__ __forceinline__ void ld_state(const StateRef& r, int d, int e0, float
 // Segment states. One workgroup walks the a.seg chunks of a segment with the
 // state in registers (16 x 16 tiles, channels a on tile rows):
 //   C <- e^{b_last} C + Kd^T v, Kd = k e^{b_last - b}
-// and leaves, per chunk, the state before it from a zero start and the
-// retention since the segment's start, and per segment the result and the
-// retention. BWD: also P = Qe^T dY (Qe = q e^b) of every chunk, walked back to
+// and leaves, per chunk, the state before it from a zero start and, with more
+// than one segment, the retention since the segment's start, and per segment
+// the result and the retention. BWD: also P = Qe^T dY (Qe = q e^b) of every chunk, walked back to
 // front at the end for the gradient of the state leaving each chunk. Bound by
 // the rows' and the states' bytes.
 // ---------------------------------------------------------------------------
@@ -670,7 +670,7 @@ __global__ __launch_bounds__(kNT, !BWD && D <= 64 ? 3 : 2) void lin_state_kernel
     if (tid < DA) {
       const float lb = (tot[0][tid] + tot[1][tid]) + (tot[2][tid] + tot[3][tid]);
       last[c - c0][tid] = lb;
-      a.gpre[at * D + a0 + tid] = fast_exp2(run);
+      if (a.nseg > 1) a.gpre[at * D + a0 + tid] = fast_exp2(run);
       run += lb;
     }
     if (c > c0) store(a.cprev + at * D * D, C);
@@ -702,15 +702,18 @@ __global__ __launch_bounds__(kNT, !BWD && D <= 64 ? 3 : 2) void lin_state_kernel
     }
   }
   const int64_t sg = (int64_t)n * a.nseg + seg;
-  store(a.segc + sg * D * D, C);
-  if (a.nseg == 1 && a.state_out) store(a.state_out + (int64_t)n * D * D, C);
-  if (tid < DA) a.segg[sg * D + a0 + tid] = fast_exp2(run);
+  if (a.nseg > 1) {
+    store(a.segc + sg * D * D, C);
+    if (tid < DA) a.segg[sg * D + a0 + tid] = fast_exp2(run);
+  } else if (a.state_out) {
+    store(a.state_out + (int64_t)n * D * D, C);
+  }
   if constexpr (BWD) {
     // P holds the last chunk's: the gradient of the state before it, from a
     // zero start after the segment. Back to front, the chunk's stored P makes
     // way for the gradient of the state leaving it.
     float suf = 0.0f;
-    if (tid < DA) {
+    if (a.nseg > 1 && tid < DA) {
       for (int c = c1 - 1; c >= c0; --c) {
         a.gsuf[((int64_t)n * a.nchunks + c) * D + a0 + tid] = fast_exp2(suf);
         suf += last[c - c0][tid];
@@ -732,7 +735,7 @@ __global__ __launch_bounds__(kNT, !BWD && D <= 64 ? 3 : 2) void lin_state_kernel
 #pragma unroll
         for (int y = 0; y < ET; ++y) P[x][y] += Q[x][y];
     }
-    store(a.segp + sg * D * D, P);
+    if (a.nseg > 1) store(a.segp + sg * D * D, P);
   }
 }
 
@@ -1626,6 +1629,8 @@ bool linear_bf16_route(int64_t heads, int nchunks, int D, bool gated, bool rope,
   if (D < (backward ? 64 : 128) || rope) return true;
   return nchunks > 16 || chunks > 256;
 }
+
+int linear_bf16_rope_row(int rope_dim) { return rope_width(rope_dim / 2); }
 
 hipError_t launch_linear_bf16_rope_table(float2* tab, int nchunks, int rope_dim, double base, hipStream_t stream) {
   const int h = rope_dim / 2;

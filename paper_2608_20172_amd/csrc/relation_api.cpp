@@ -1217,10 +1217,10 @@ static int linear_segments(const rel_problem* p) {
 // problems of 64 channels per head (split): its chunk states are those of
 // 4 B H heads of width 64, and it adds qt and kt of every row and eight
 // planes of partial gradients (fp32, [B H, T, 128] each).
-// With bf16 inputs (linear_bf16.hip) the states are kept per chunk from a zero
-// start at its segment and per segment; a segment of one chunk needs the latter
-// only. Longer segments get the room of two-chunk ones, the largest need, so
-// that a workspace sized for a sequence serves every shorter one.
+// linear_bf16.hip's kernels keep the states per chunk from a zero start at its
+// segment and, with more than one segment, per segment; segments of one chunk
+// need the latter only. Longer segments get the room of two-chunk ones, the
+// largest need, so that a workspace sized for a sequence serves every shorter one.
 struct LinearPlan {
   size_t dstate, gamma, cprev, segc, segg, total;  // forward
   size_t pstate, gout, segp, total_bwd;            // backward
@@ -1228,6 +1228,7 @@ struct LinearPlan {
   size_t gpart, total_gated;                       // gated backward: the gate's segment sums
   size_t gpre, gsuf;                               // bf16: retention before and after a chunk in its segment
   int seg, nseg;                                   // bf16: chunks per segment, segments
+  size_t rope, end;                                // the RoPE table, and the end of everything the call uses
 };
 
 static bool linear_split(const rel_problem* p) { return p->D == 128; }
@@ -1238,7 +1239,8 @@ static LinearPlan plan_linear_bf16(const rel_problem* p) {
   L.seg = rel::linear_bf16_segment((int64_t)N, (int)nc);
   L.nseg = (int)((nc + L.seg - 1) / L.seg);
   const size_t chunks = L.seg > 1 ? N * nc * D * D * 4 : 0;  // bytes before the segments' states
-  const size_t states = align256(N * (L.seg > 1 ? nc + (nc + 1) / 2 : nc) * D * D * 4), rows = align256(N * nc * D * 4);
+  const size_t segments = L.nseg > 1 ? N * (L.seg > 1 ? (nc + 1) / 2 : nc) * D * D * 4 : 0;
+  const size_t states = align256(chunks + segments), rows = L.nseg > 1 ? align256(N * nc * D * 4) : 0;
   L.cprev = 0;
   L.segc = chunks;
   L.gpre = states;
@@ -1254,8 +1256,7 @@ static LinearPlan plan_linear_bf16(const rel_problem* p) {
   return L;
 }
 
-// The plan of linear.hip's kernels. It needs at least what the bf16 plan needs,
-// so every workspace query and check takes its size.
+// The plan of linear.hip's kernels.
 static LinearPlan plan_linear(const rel_problem* p, bool split) {
   LinearPlan L{};
   const size_t N = (size_t)(p->B * p->H) * (split ? 4 : 1), nc = (size_t)linear_chunks(p);
@@ -1321,12 +1322,6 @@ static void set_linear_workspace(rel::LinearArgs& a, const LinearPlan& L, char* 
   }
 }
 
-size_t relation_linear_fwd_workspace_bytes(const rel_problem* p) {
-  bool empty = false;
-  if (check_linear(p, &empty) != REL_OK || empty) return 0;
-  return plan_linear(p, false).total;
-}
-
 // RoPE of the gated entry points: rope_dim 0 (none), or an even width up to D
 // whose channels j < rope_dim / 2 turn with j + rope_dim / 2; at D = 128 (the
 // four-block backward, whose row passes hold 4 channels per lane) a multiple of 8.
@@ -1348,15 +1343,38 @@ static bool linear_bf16(const rel_problem* p, bool gated, bool rope, bool backwa
          rel::linear_bf16_route(p->B * p->H, linear_chunks(p), (int)p->D, gated, rope, backward);
 }
 
-static size_t rope_table_bytes(const rel_problem* p, int32_t rope_dim) {
+// What a call uses with the kernels of linear_bf16.hip (bf16) or linear.hip. The
+// RoPE table, whose rows differ between the two, comes last.
+static LinearPlan linear_plan(const rel_problem* p, bool bf16, bool backward, bool gated, int32_t rope_dim) {
+  LinearPlan L = bf16 ? plan_linear_bf16(p) : plan_linear(p, backward && linear_split(p));
   const size_t rows = (size_t)linear_chunks(p) + (size_t)rel::linear_chunk();
-  return rope_dim > 0 ? align256(rows * (size_t)(rope_dim / 2) * 8) : 0;
+  const size_t entries = (size_t)(bf16 ? rel::linear_bf16_rope_row(rope_dim) : rope_dim / 2);
+  L.rope = !backward ? L.total : gated ? L.total_gated : L.total_bwd;
+  L.end = L.rope + (rope_dim > 0 ? align256(rows * entries * 8) : 0);
+  return L;
 }
 
-size_t relation_linear_gated_fwd_workspace_bytes(const rel_problem* p, int32_t rope_dim) {
+// The workspace a call needs: the larger of the two files' plans for bf16,
+// whichever takes the problem, so that the size for a sequence serves every
+// shorter one.
+static size_t linear_need(const rel_problem* p, bool backward, bool gated, int32_t rope_dim) {
+  const size_t a = linear_plan(p, false, backward, gated, rope_dim).end;
+  return p->dtype == REL_BF16 ? std::max(a, linear_plan(p, true, backward, gated, rope_dim).end) : a;
+}
+
+static size_t linear_ws(const rel_problem* p, bool backward, bool gated, int32_t rope_dim) {
   bool empty = false;
   if (check_linear(p, &empty) != REL_OK || empty || check_rope(p, rope_dim, 1.0f) != REL_OK) return 0;
-  return plan_linear(p, false).total + rope_table_bytes(p, rope_dim);
+  return linear_need(p, backward, gated, rope_dim);
+}
+
+size_t relation_linear_fwd_workspace_bytes(const rel_problem* p) { return linear_ws(p, false, false, 0); }
+size_t relation_linear_gated_fwd_workspace_bytes(const rel_problem* p, int32_t rope_dim) {
+  return linear_ws(p, false, true, rope_dim);
+}
+size_t relation_linear_bwd_workspace_bytes(const rel_problem* p) { return linear_ws(p, true, false, 0); }
+size_t relation_linear_gated_bwd_workspace_bytes(const rel_problem* p, int32_t rope_dim) {
+  return linear_ws(p, true, true, rope_dim);
 }
 
 // The RoPE table (cos, sin at the chunk starts and at the offsets inside a
@@ -1393,8 +1411,7 @@ static rel_status linear_fwd_impl(const rel_problem* p, const void* p1, const vo
   REL_TRY(check_aligned(dt_bias, 4, "dt_bias", false));
   REL_TRY(check_aligned(out, es, "out", true));
   REL_TRY(check_aligned(state_out, 4, "state_out", false));
-  const LinearPlan L = plan_linear(p, false);
-  const size_t need = L.total + rope_table_bytes(p, rope_dim);
+  const size_t need = linear_need(p, false, a_log != nullptr, rope_dim);
   if (!workspace || workspace_bytes < need)
     return fail(REL_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
                 workspace ? workspace_bytes : (size_t)0);
@@ -1423,9 +1440,10 @@ static rel_status linear_fwd_impl(const rel_problem* p, const void* p1, const vo
   a.nchunks = linear_chunks(p);
   a.nseg = linear_segments(p);
   a.vec16 = linear_vec16(p, {p1, p2, v, a_log, dt_bias}, g);
-  const LinearPlan W = linear_bf16(p, a_log != nullptr, rope_dim > 0, false) ? plan_linear_bf16(p) : L;
-  set_linear_workspace(a, W, (char*)workspace, false);
-  REL_TRY(set_rope(a, p, rope_dim, rope_base, (char*)workspace, W.total, (hipStream_t)stream));
+  const bool gated = a_log != nullptr;
+  const LinearPlan L = linear_plan(p, linear_bf16(p, gated, rope_dim > 0, false), false, gated, rope_dim);
+  set_linear_workspace(a, L, (char*)workspace, false);
+  REL_TRY(set_rope(a, p, rope_dim, rope_base, (char*)workspace, L.rope, (hipStream_t)stream));
   const hipError_t e = rel::launch_linear_fwd(a, p->dtype, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "Linear Relation launch");
   return REL_OK;
@@ -1445,18 +1463,6 @@ rel_status relation_linear_gated_fwd(const rel_problem* p, const void* p1, const
   if (!a_log || !dt_bias) return fail(REL_ERR_INVALID_ARG, "a_log and dt_bias are required");
   return linear_fwd_impl(p, p1, p2, v, r, a_log, dt_bias, rope_dim, rope_base, out, state_out, workspace,
                          workspace_bytes, stream);
-}
-
-static size_t linear_bwd_ws(const rel_problem* p, bool gated, int32_t rope_dim) {
-  bool empty = false;
-  if (check_linear(p, &empty) != REL_OK || empty || check_rope(p, rope_dim, 1.0f) != REL_OK) return 0;
-  const LinearPlan L = plan_linear(p, linear_split(p));
-  return (gated ? L.total_gated : L.total_bwd) + rope_table_bytes(p, rope_dim);
-}
-
-size_t relation_linear_bwd_workspace_bytes(const rel_problem* p) { return linear_bwd_ws(p, false, 0); }
-size_t relation_linear_gated_bwd_workspace_bytes(const rel_problem* p, int32_t rope_dim) {
-  return linear_bwd_ws(p, true, rope_dim);
 }
 
 // g: the log-retention, or with a_log set the gate's pre-activation r; dg is
@@ -1486,7 +1492,7 @@ static rel_status linear_bwd_impl(const rel_problem* p, const void* p1, const vo
     REL_TRY(check_aligned(da_log, 4, "da_log", true));
     REL_TRY(check_aligned(ddt_bias, 4, "ddt_bias", true));
   }
-  const size_t need = linear_bwd_ws(p, gated, rope_dim);
+  const size_t need = linear_need(p, true, gated, rope_dim);
   if (!workspace || workspace_bytes < need)
     return fail(REL_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
                 workspace ? workspace_bytes : (size_t)0);
@@ -1510,7 +1516,7 @@ static rel_status linear_bwd_impl(const rel_problem* p, const void* p1, const vo
                             {ddt_bias, pb, false, true, "ddt_bias"},
                             {workspace, need, false, true, "workspace"}}));
   if (test_fail_launch()) return fail(REL_ERR_HIP, "launch failure injected by RELATION_TEST_FAIL_LAUNCH");
-  const LinearPlan L = linear_bf16(p, gated, rope_dim > 0, true) ? plan_linear_bf16(p) : plan_linear(p, linear_split(p));
+  const LinearPlan L = linear_plan(p, linear_bf16(p, gated, rope_dim > 0, true), true, gated, rope_dim);
   rel::LinearArgs a{};
   a.p1 = p1; a.p2 = p2; a.v = v; a.g = g; a.dy = dout;
   a.dp1 = dp1; a.dp2 = dp2; a.dv = dv; a.dg = dg;
@@ -1527,8 +1533,7 @@ static rel_status linear_bwd_impl(const rel_problem* p, const void* p1, const vo
     a.gpart = (float*)((char*)workspace + L.gpart);
     a.da_log = da_log; a.ddt_bias = ddt_bias;
   }
-  REL_TRY(set_rope(a, p, rope_dim, rope_base, (char*)workspace, gated ? L.total_gated : L.total_bwd,
-                   (hipStream_t)stream));
+  REL_TRY(set_rope(a, p, rope_dim, rope_base, (char*)workspace, L.rope, (hipStream_t)stream));
   const hipError_t e = rel::launch_linear_bwd(a, p->dtype, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "Linear Relation backward launch");
   return REL_OK;

@@ -3,6 +3,7 @@ fp64 oracle's token-by-token recurrence, on the same seeded inputs. fp32:
 max-abs <= 1e-4; bf16: relative l2 <= 2e-2."""
 from __future__ import annotations
 
+import ctypes
 import math
 
 import numpy as np
@@ -396,6 +397,21 @@ def test_linear_gated_rope(width, padded, T, dtype):
         da_terms[0, h], dt_terms[0, h] = ref_b["dg"] * g, gb["dr"]
     _assert_param_grad("da_log", _np(o["da_log"])[:, :width], da_ref, da_terms, dtype)
     _assert_param_grad("ddt_bias", _np(o["ddt_bias"])[:, :width], dt_ref, dt_terms, dtype)
+
+
+@pytest.mark.parametrize("rope", [24, 26, 28, 30, 32])
+def test_linear_workspace_guard(rope):
+    """Nothing past the queried workspace is written where the RoPE table is
+    most of it (one head, one chunk, width 32)."""
+    x = _prep(1, 1, 64, 32, "bf16", seed=2250 + rope)
+    p = R.make_problem(x["p1"])
+    query = R.load_library().relation_linear_gated_fwd_workspace_bytes
+    size = query(ctypes.byref(p), rope)
+    buf = torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    a_log, dt_bias = (torch.from_numpy(z).cuda() for z in _gate_params(1, 32, 2251))
+    R.relation_linear_gated_fwd(x["p1"], x["p2"], x["v"], x["g"], a_log, dt_bias, rope_dim=rope, workspace=buf[:size])
+    torch.cuda.synchronize()
+    assert bool((buf[size:] == 0xA5).all())
 
 
 @pytest.mark.parametrize("H,T,D,steep", [
