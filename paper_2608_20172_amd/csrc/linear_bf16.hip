@@ -1479,32 +1479,7 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
     }
   }
 
-  // ---- through q = S ^p1, k = S ^p2 (rotated), S = sigmoid(scale p1 . p2 / tau_S)
-  const float iS = 1.0f / o.S;
-  float ds = 0.0f, h1 = 0.0f, h2 = 0.0f;
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      o.q[s][u] *= iS;  // ^p1, ^p2
-      o.k[s][u] *= iS;
-      h1 = __builtin_fmaf(o.q[s][u], dq[s][u], h1);
-      h2 = __builtin_fmaf(o.k[s][u], dk[s][u], h2);
-    }
-  h1 = sum_groups(h1);
-  h2 = sum_groups(h2);
-  ds = h1 + h2;
-  const float dU = ds * o.S * (1.0f - o.S) * a.scale * a.inv_tau;
-  // |p1| = 1 / in1 (0 where p1 = 0)
-  const float n1 = o.in1 > 0.0f ? 1.0f / o.in1 : 0.0f, n2 = o.in2 > 0.0f ? 1.0f / o.in2 : 0.0f;
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const float p1 = o.q[s][u], p2 = o.k[s][u];
-      dq[s][u] = dU * p2 * n2 + o.S * (dq[s][u] - p1 * h1) * o.in1;
-      dk[s][u] = dU * p1 * n1 + o.S * (dk[s][u] - p2 * h2) * o.in2;
-    }
+  // ---- back through the rotation
   if (a.rope) {
     const int tc = min(t, a.T - 1), h = a.rope_half;
     if (NS >= 2 && 2 * h == D) {
@@ -1551,6 +1526,37 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
       }
     }
   }
+  // ---- through q = S ^p1, k = S ^p2, S = sigmoid(scale p1 . p2 / tau_S): the
+  // rows once more, as S may be 0 and q and k then hold nothing of them
+  {
+    const unsigned off = (unsigned)min(t, a.T - 1) * (unsigned)a.st + 8u * L.g;
+    const bf16 *P1 = (const bf16*)a.p1 + head_off(a, n), *P2 = (const bf16*)a.p2 + head_off(a, n);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      unpack8(ld_row<VEC>(P1 + (off + 32u * s)), o.q[s]);
+      unpack8(ld_row<VEC>(P2 + (off + 32u * s)), o.k[s]);
+    }
+  }
+  float h1 = 0.0f, h2 = 0.0f;
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      h1 = __builtin_fmaf(o.q[s][u], dq[s][u], h1);
+      h2 = __builtin_fmaf(o.k[s][u], dk[s][u], h2);
+    }
+  h1 = sum_groups(h1) * o.in1;  // ^p1 . dq
+  h2 = sum_groups(h2) * o.in2;
+  const float dU = (h1 + h2) * o.S * (1.0f - o.S) * a.scale * a.inv_tau;
+  const float f1 = o.S * o.in1, f2 = o.S * o.in2;
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float p1 = o.q[s][u], p2 = o.k[s][u];
+      dq[s][u] = __builtin_fmaf(dU, p2, f1 * (dq[s][u] - p1 * o.in1 * h1));
+      dk[s][u] = __builtin_fmaf(dU, p1, f2 * (dk[s][u] - p2 * o.in2 * h2));
+    }
   if (ok) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {

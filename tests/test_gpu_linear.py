@@ -399,6 +399,35 @@ def test_linear_gated_rope(width, padded, T, dtype):
     _assert_param_grad("ddt_bias", _np(o["ddt_bias"])[:, :width], dt_ref, dt_terms, dtype)
 
 
+@pytest.mark.parametrize("H,T,D", [(2, 80, 32), (1, 100, 64), (1, 17 * 64 + 5, 64), (1, 100, 128), (10, 17 * 64 - 3, 128)])
+def test_linear_backward_vanishing_self(H, T, D):
+    """Rows with p2 = -f p1, whose Self S = sigmoid(-f |p1|^2 / (2 sqrt(D))) is
+    small (f = 8: about 2^-33 to 2^-65), tiny (16) or 0 in fp32 (64): dp1 and dp2
+    of every such row against the oracle, finite where S is 0. A row's terms are
+    products of 32-bit values; only dp1 and dp2 are rounded to bf16 (2^-9). S, the
+    gradient dU of its argument and S / |p| count as 0 below 2^-126: times the rows
+    that they multiply, p1 and p2 for dU and the gradients of ^p1 and ^p2 (norms
+    below 32 here) for S / |p|."""
+    x = _prep(1, H, T, D, "bf16", seed=2260 + T + D, gmax=0.05)
+    t = np.arange(T)
+    for r, f in ((1, 8.0), (3, 16.0), (5, 64.0)):
+        x["p2"][:, :, t % 8 == r] = -f * x["p1"][:, :, t % 8 == r]
+    x["p2r"] = _np(x["p2"])
+    log(f"[linear vanishing self] H={H} T={T} D={D}")
+    o = R.relation_linear_bwd(x["p1"], x["p2"], x["v"], x["g"], x["dy"])
+    torch.cuda.synchronize()
+    for h in (0, H - 1):
+        ref = LO.backward(x["p1r"][0, h], x["p2r"][0, h], x["vr"][0, h], x["gr"][0, h], x["dyr"][0, h])
+        for n in ("dp1", "dp2", "dv", "dg"):
+            assert_close(f"{n}[0,{h}]", _np(o[n])[0, h], ref[n], "bf16")
+        for n in ("dp1", "dp2"):
+            got = _np(o[n])[0, h]
+            err = np.linalg.norm(got - ref[n], axis=1)
+            rows = np.linalg.norm(x["p1r"][0, h], axis=1) + np.linalg.norm(x["p2r"][0, h], axis=1) + 32.0
+            lim = 2.0 ** -8 * np.linalg.norm(ref[n], axis=1) + 2.0 ** -126 * rows
+            assert np.all(err <= lim), f"{n}[0,{h}]: rows {np.flatnonzero(~(err <= lim))[:8]}, {np.max(err / lim)}"
+
+
 @pytest.mark.parametrize("rope", [24, 26, 28, 30, 32])
 def test_linear_workspace_guard(rope):
     """Nothing past the queried workspace is written where the RoPE table is
