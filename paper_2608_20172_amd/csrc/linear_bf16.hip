@@ -357,7 +357,7 @@ __device__ __forceinline__ void use_raw(const LinearArgs& a, int n, int t, bool 
   s11 = sum_groups(s11);
   s22 = sum_groups(s22);
   s12 = sum_groups(s12);
-  o.S = fast_rcp(1.0f + fast_exp2(-s12 * a.scale * a.inv_tau * kLog2e));
+  o.S = 1.0f / (1.0f + expf(-s12 * a.scale * a.inv_tau));
   o.in1 = s11 > 0.0f ? rsqrtf(s11) : 0.0f;
   o.in2 = s22 > 0.0f ? rsqrtf(s22) : 0.0f;
 #pragma unroll
@@ -550,7 +550,7 @@ __device__ __forceinline__ void ld_state(const StateRef& r, int d, int e0, float
 constexpr int kMaxSeg = 8;
 
 template <int D, bool BWD, bool VEC>
-__global__ __launch_bounds__(kNT, !BWD && D <= 64 ? 3 : 2) void lin_state_kernel(LinearArgs a) {
+__global__ __launch_bounds__(kNT, D == 32 || (!BWD && D == 64) ? 3 : 2) void lin_state_kernel(LinearArgs a) {
   // at D = 128 two workgroups (blockIdx.z) share a segment, 64 of the state's
   // rows each: the registers of a whole one do not fit two waves per SIMD
   constexpr int DA = D < 64 ? D : 64;  // the workgroup's channels a

@@ -428,6 +428,31 @@ def test_linear_backward_vanishing_self(H, T, D):
             assert np.all(err <= lim), f"{n}[0,{h}]: rows {np.flatnonzero(~(err <= lim))[:8]}, {np.max(err / lim)}"
 
 
+def test_linear_self_accuracy():
+    """S keeps its 24 bits where it is small. Two tokens of width 32 whose p1 . p2
+    are whole numbers and scale / tau_s a power of two, so that S's argument, -37
+    to -76, is exact: the second token's dg is S times factors of a few roundings
+    each. The exponential, the division and the reciprocal square roots are within
+    2 units of 2^-24, there are about eight further roundings, and the sum of 32
+    positive products dY . v adds up to 8."""
+    H, D = 16, 32
+    p1 = np.ones((1, H, 2, D))
+    p2 = np.ones((1, H, 2, D))
+    for h in range(H):
+        p2[0, h, 1] = -(600.0 + 40 * h) / D
+    rng = np.random.default_rng(2270)
+    rnd = lambda: np.abs(rng.standard_normal((1, H, 2, D)))
+    (p1, p1r), (p2, p2r), (v, vr), (dy, dyr) = (to_device(z, "bf16") for z in (p1, p2, rnd(), rnd()))
+    g = torch.zeros((1, H, 2, D), device="cuda")
+    o = R.relation_linear_bwd(p1, p2, v, g, dy, scale=0.125)
+    torch.cuda.synchronize()
+    for h in range(H):
+        ref = LO.backward(p1r[0, h], p2r[0, h], vr[0, h], np.zeros((2, D)), dyr[0, h], scale=0.125)
+        err = np.max(np.abs(_np(o["dg"])[0, h, 1] / ref["dg"][1] - 1.0))
+        log(f"  S argument {-(600 + 40 * h) / 16}: dg relative error {err:.1e}")
+        assert err <= 24 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("rope", [24, 26, 28, 30, 32])
 def test_linear_workspace_guard(rope):
     """Nothing past the queried workspace is written where the RoPE table is
