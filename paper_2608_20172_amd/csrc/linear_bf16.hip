@@ -24,7 +24,9 @@
 // spans a whole block between the pair, whose true factor is smaller than 2^-90.
 // A channel with a larger range takes one-sided references (factors <= 1)
 // towards the other blocks, and the block's own pairs take it term by term, with
-// the exact exponent, beside the matrix product over the other channels.
+// the exact exponent, beside the matrix product over the other channels. Chunks
+// without a range over kSteep, most of them where the gate retains, take a path
+// that knows no such channels.
 //
 // Precision. Products that reach the decay gradient (dq, dk, C0, G) keep fp32
 // accuracy: an fp32 operand is split as hi + mid + lo, three bf16 numbers that
@@ -34,13 +36,16 @@
 #include "kernels.h"
 #include "lanes.h"
 
+#include <type_traits>
+
 namespace rel {
 
 namespace {
 
 constexpr int kL = 64;       // tokens per chunk
 constexpr int kNT = 256;     // threads per workgroup
-constexpr float kRange = 200.0f;  // log2 units of decay over a block that is still factored at its middle
+constexpr float kSteep = 64.0f;   // log2 units of decay over a block past which a chunk takes its kernel's path for steep channels
+constexpr float kRange = 200.0f;  // log2 units over a block past which that path takes a channel term by term
 
 typedef bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -472,6 +477,17 @@ __device__ __forceinline__ void last_b(const float (*tot)[D], int s, const LaneI
   }
 }
 
+// Whether some channel of some block decays by more than 2^kSteep from the row
+// before the block to its last (or by NaN): from the blocks' totals of scan_b, the
+// same in every wave of the workgroup.
+template <int D>
+__device__ __forceinline__ bool chunk_steep(const float (*tot)[D]) {
+  bool over = false;
+#pragma unroll
+  for (int x = 0; x < 4 * D / 64; ++x) over |= !(-(&tot[0][0])[64 * x + (int)(threadIdx.x & 63)] <= kSteep);
+  return wave_any(over);
+}
+
 // Bit 8 s + u (wave-uniform): the block's range of b is over kRange (or NaN) at
 // element u of piece s in some lane group, four channels that then go term by term.
 template <int D>
@@ -485,11 +501,6 @@ __device__ __forceinline__ unsigned block_over(const Own<D / 32>& o) {
   return __builtin_amdgcn_readfirstlane(over);
 }
 __device__ __forceinline__ bool is_over(unsigned over, int s, int u) { return (over >> (8 * s + u)) & 1; }
-
-// Value `v` (0..3, wave-uniform) of x, from another lane.
-__device__ __forceinline__ float pick_lane(const floatx4& x, int v, int lane) {
-  return __shfl(v == 0 ? x[0] : v == 1 ? x[1] : v == 2 ? x[2] : x[3], lane, 64);
-}
 
 // Where the states of chunk c are. Within a segment of a.seg chunks the state
 // kernel leaves every chunk's state from a zero start at the segment's first
@@ -801,13 +812,91 @@ __global__ __launch_bounds__(kNT) void lin_scan_kernel(LinearArgs a) {
   if (!rev && a.state_out && w == 0) a.state_out[n * DD + idx] = carry;
 }
 
-// One element's part of the scores of a block's own pairs, term by term: r +=
-// own x_t y_j e^{b_t - b_j}, from the other row x (0..15, wave-uniform) with
-// value ox, summed over the lane groups into x's place of the block.
-__device__ __forceinline__ void add_exact_score(floatx4& r, int x, float term, const LaneIx& L) {
-  const float sc = sum_groups(term);
+// A block's own pairs, term by term, for one channel of the lane's row with
+// exponent b: offset X + x, x < N, pairs the row with row i - X - x (or i + X + x,
+// LATER) of the block, whose value `other` comes by a row shift. y = other
+// e^{b_t - b_j}, 0 past the block's ends, goes to grad += d[x] y and P[x] += own y.
+// Through ds_bpermute, and with a sum over the lane groups per channel and
+// offset, a step of 16 heads x 4096 with every channel steep took 141, 309 and 767
+// us at width 32, 64 and 128 (linear.hip's kernels: 118, 184, 729); so 79, 159, 492.
+template <bool LATER, bool GRAD, bool SCORE, int X, int N, int x = 0>
+__device__ __forceinline__ void exact_terms(int i, float own, float other, float b, const float (&d)[N], float& grad,
+                                            float (&P)[N]) {
+  constexpr int CTRL = (LATER ? 0x100 : 0x110) + X + x;  // row_shl, row_shr
+  const float bx = dpp_shift<CTRL>(b);
+  const float e = dpp_shift<CTRL>(other) * fast_exp2(LATER ? bx - b : b - bx);
+  const float y = (LATER ? i < 16 - X - x : i >= X + x) ? e : 0.0f;
+  if (GRAD) grad = __builtin_fmaf(d[x], y, grad);
+  if (SCORE) P[x] = __builtin_fmaf(own, y, P[x]);
+  if constexpr (x + 1 < N) exact_terms<LATER, GRAD, SCORE, X, N, x + 1>(i, own, other, b, d, grad, P);
+}
+// The same for every channel of `over`, offsets X .. 15 in runs of N: grad +=
+// z' y with z' the block z (4 rows or columns per lane group) at the offset, r
+// the scores' block. N = 0: a piece of eight channels and one offset at a time, in
+// a loop that shifts the other rows on by one, for the width-128 gradient kernel,
+// whose common path the registers of unrolled runs slow down (a step of 16 heads x
+// 4096 without steep channels 450 us with runs of 3, 399 so).
+template <bool LATER, bool GRAD, bool SCORE, int NS, int N, int X = 1>
+__device__ __forceinline__ void exact_block(unsigned over, const LaneIx& L, const float (&own)[NS][8],
+                                            const float (&other)[NS][8], const float (&b)[NS][8], const floatx4& z,
+                                            float (&grad)[NS][8], floatx4& r) {
+  static_assert(N == 0 || (16 - X) % N == 0, "whole runs");
+  constexpr int M = N ? N : 1;
+  auto pick = [&](int at) __attribute__((always_inline)) {  // z at the row's column (or row) `at`, to all its lane groups
+    const float lo = at & 1 ? z[1] : z[0], hi = at & 1 ? z[3] : z[2];
+    return __shfl(at & 2 ? hi : lo, L.i + 16 * ((at >> 2) & 3), 64);
+  };
+  auto put = [&](int at, float p) __attribute__((always_inline)) {
+    const float sc = sum_groups(p);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) r[v] += x == 4 * L.g + v ? sc : 0.0f;
+    for (int v = 0; v < 4; ++v) r[v] += at == 4 * L.g + v ? sc : 0.0f;
+  };
+  float d[M], P[M];
+  if constexpr (N == 0) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if ((over >> (8 * s)) & 255u) {  // the piece's eight channels together: their chains overlap
+        float ox[8], bx[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          ox[u] = other[s][u];
+          bx[u] = b[s][u];
+        }
+#pragma unroll 1
+        for (int x = 1; x < 16; ++x) {
+          const int at = LATER ? L.i + x : L.i - x;
+          if (GRAD) d[0] = pick(at);
+          P[0] = 0.0f;
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            ox[u] = dpp_shift<(LATER ? 0x101 : 0x111)>(ox[u]);
+            bx[u] = dpp_shift<(LATER ? 0x101 : 0x111)>(bx[u]);
+            const float e = ox[u] * fast_exp2(LATER ? bx[u] - b[s][u] : b[s][u] - bx[u]);
+            const float y = (at & 15) == at && is_over(over, s, u) ? e : 0.0f;
+            if (GRAD) grad[s][u] = __builtin_fmaf(d[0], y, grad[s][u]);
+            if (SCORE) P[0] = __builtin_fmaf(own[s][u], y, P[0]);
+          }
+          if (SCORE) put(at, P[0]);
+        }
+      }
+  } else {
+#pragma unroll
+    for (int x = 0; x < M; ++x) {
+      P[x] = 0.0f;
+      if (GRAD) d[x] = pick(LATER ? L.i + X + x : L.i - X - x);
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (is_over(over, s, u))
+          exact_terms<LATER, GRAD, SCORE, X, N>(L.i, own[s][u], other[s][u], b[s][u], d, grad[s][u], P);
+    if (SCORE) {
+#pragma unroll
+      for (int x = 0; x < M; ++x) put(LATER ? L.i + X + x : L.i - X - x, P[x]);
+    }
+    if constexpr (X + N < 16) exact_block<LATER, GRAD, SCORE, NS, N, X + N>(over, L, own, other, b, z, grad, r);
+  }
 }
 
 // Per chunk: Y_t = v_t + sum_{j < t} A_tj v_j + Qe C0.
@@ -820,7 +909,6 @@ __global__ __launch_bounds__(kNT, D <= 64 ? 3 : 2) void lin_out_kernel(LinearArg
   __shared__ __attribute__((aligned(1024))) unsigned char CS[D * RB];  // the state entering the chunk
   __shared__ float tot[4][D], bnd[4][D];
   const LaneIx L;
-  const int lane = threadIdx.x & 63;
   const int c = blockIdx.x, n = blockIdx.y, tid = threadIdx.x;
   const int row = 16 * L.w + L.i, t = c * kL + row;
   const bool ok = t < a.T;
@@ -844,7 +932,6 @@ __global__ __launch_bounds__(kNT, D <= 64 ? 3 : 2) void lin_out_kernel(LinearArg
   use_raw<D, NS, false, VEC, true>(a, n, t, ok, 0, L, KE, V, raw, o);
   float off[NS][8];
   scan_b<D>(o, tot, L, off);
-  const unsigned over = block_over<D>(o);
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     float x[8], e[8];
@@ -885,35 +972,31 @@ __global__ __launch_bounds__(kNT, D <= 64 ? 3 : 2) void lin_out_kernel(LinearArg
     }
     add_block(jb, at);
   }
-  floatx4 at = {};
+  // the block's own pairs
+  auto own_block = [&](auto steep) __attribute__((always_inline)) {
+    constexpr bool STEEP = decltype(steep)::value;
+    const unsigned over = STEEP ? block_over<D>(o) : 0;
+    floatx4 at = {};
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    float x[8], y[8];
+    for (int s = 0; s < NS; ++s) {
+      float x[8], y[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const float d = o.b[s][u] - 0.5f * (bcast16<0>(o.b[s][u]) + bcast16<15>(o.b[s][u]));
-      x[u] = is_over(over, s, u) ? 0.0f : o.q[s][u] * fast_exp2(d);
-      y[u] = is_over(over, s, u) ? 0.0f : o.k[s][u] * fast_exp2(-d);
+      for (int u = 0; u < 8; ++u) {
+        const float d = o.b[s][u] - 0.5f * (bcast16<0>(o.b[s][u]) + bcast16<15>(o.b[s][u]));
+        x[u] = STEEP && is_over(over, s, u) ? 0.0f : o.q[s][u] * fast_exp2(d);
+        y[u] = STEEP && is_over(over, s, u) ? 0.0f : o.k[s][u] * fast_exp2(-d);
+      }
+      at = mm32(pack8(y), pack8(x), at);
     }
-    at = mm32(pack8(y), pack8(x), at);
-  }
 #pragma unroll
-  for (int v = 0; v < 4; ++v) at[v] = 4 * L.g + v < L.i ? at[v] : 0.0f;
-  if (over) {
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (is_over(over, s, u)) {
-#pragma unroll 1
-          for (int x = 0; x < 15; ++x) {
-            const float kx = __shfl(o.k[s][u], (lane & 48) | x, 64), bx = __shfl(o.b[s][u], (lane & 48) | x, 64);
-            const float y = o.q[s][u] * kx * fast_exp2(o.b[s][u] - bx);
-            add_exact_score(at, x, x < L.i ? y : 0.0f, L);
-          }
-        }
-  }
-  add_block(L.w, at);
+    for (int v = 0; v < 4; ++v) at[v] = 4 * L.g + v < L.i ? at[v] : 0.0f;
+    if constexpr (STEEP) {
+      if (over) exact_block<false, false, true, NS, D == 128 ? 3 : 15>(over, L, o.q, o.k, o.b, at, o.q, at);
+    }
+    add_block(L.w, at);
+  };
+  if (chunk_steep<D>(tot)) own_block(std::true_type{});
+  else own_block(std::false_type{});
   if (inter) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -985,7 +1068,6 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
   __shared__ float tot[4][D], ck[4][D], cq[4][D], ek[3][D], eq[3][D], gm[D], pt[4][D], ex[4][D], lst[D];
   unsigned char* VY = R + 3 * PS;
   const LaneIx L;
-  const int lane = threadIdx.x & 63;
   const int c = blockIdx.x, n = blockIdx.y, tid = threadIdx.x;
   const int row = 16 * L.w + L.i, t = c * kL + row;
   const bool ok = t < a.T;
@@ -1003,12 +1085,13 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
       dyo[s] = raw.dy[s];
     }
   }
-  unsigned over;
+  float off[NS][8];
+  scan_b<D>(o, tot, L, off);
+  auto rest = [&](auto steep) __attribute__((always_inline)) {
+  constexpr bool STEEP = decltype(steep)::value;
+  const unsigned over = STEEP ? block_over<D>(o) : 0;
   {
-    float off[NS][8];
-    scan_b<D>(o, tot, L, off);
     if (tid < D) lst[tid] = (tot[0][tid] + tot[1][tid]) + (tot[2][tid] + tot[3][tid]);  // b_last
-    over = block_over<D>(o);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       float k8[8], q8[8];
@@ -1016,8 +1099,8 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
       for (int u = 0; u < 8; ++u) {
         const float b0 = bcast16<0>(o.b[s][u]), b1 = bcast16<15>(o.b[s][u]);
         const float mid = 0.5f * (b0 + b1);
-        k8[u] = is_over(over, s, u) ? b1 : mid;
-        q8[u] = is_over(over, s, u) ? off[s][u] : mid;
+        k8[u] = STEEP && is_over(over, s, u) ? b1 : mid;
+        q8[u] = STEEP && is_over(over, s, u) ? off[s][u] : mid;
       }
       if (L.i == 0) {
         st8f(&ck[L.w][32 * s + 8 * L.g], k8);
@@ -1028,7 +1111,7 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
   float* qsave = a.qn + ((int64_t)n * a.T + min(t, a.T - 1)) * D + 8 * L.g;  // q of a block with steep channels
   // q is not held through the last phases at D >= 64 (registers)
   constexpr bool KEEP_Q = D < 64;
-  if (!KEEP_Q && over && ok) {
+  if (STEEP && !KEEP_Q && over && ok) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) st8f(qsave + 32 * s, o.q[s]);
   }
@@ -1176,25 +1259,11 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
       ld8f(&ck[L.w][32 * s + 8 * L.g], r8);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const float f = is_over(over, s, u) ? 0.0f : fast_exp2(o.b[s][u] - r8[u]);
+        const float f = STEEP && is_over(over, s, u) ? 0.0f : fast_exp2(o.b[s][u] - r8[u]);
         dq[s][u] = __builtin_fmaf(acc[2 * s + (u >> 2)][u & 3], f, dq[s][u]);
       }
     }
-    if (over) {
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (is_over(over, s, u)) {
-#pragma unroll 1
-            for (int x = 0; x < 15; ++x) {
-              const float dA = pick_lane(z, x & 3, L.i + 16 * (x >> 2));
-              const float kx = __shfl(o.k[s][u], (lane & 48) | x, 64), bx = __shfl(o.b[s][u], (lane & 48) | x, 64);
-              const float y = dA * kx * fast_exp2(o.b[s][u] - bx);
-              dq[s][u] += x < L.i ? y : 0.0f;
-            }
-          }
-    }
+    if (STEEP && over) exact_block<false, true, false, NS, D == 128 ? 0 : 15>(over, L, o.q, o.k, o.b, z, dq, z);
   }
   __syncthreads();  // the region is free
 
@@ -1353,7 +1422,7 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const float f = is_over(over, s, u) ? 0.0f : fast_exp2(r8[u] - o.b[s][u]);
+        const float f = STEEP && is_over(over, s, u) ? 0.0f : fast_exp2(r8[u] - o.b[s][u]);
         x[u] = o.k[s][u] * f;
         dk[s][u] = __builtin_fmaf(acc[2 * s + (u >> 2)][u & 3], f, dk[s][u]);
         if constexpr (!KEEP_Q) o.q[s][u] = ((l[u] + m[u]) + h[u]) * f;
@@ -1362,27 +1431,16 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) s4[v] = 4 * L.g + v > L.i ? s4[v] : 0.0f;
-    if (over) {
+    if (STEEP && over) {
+      if constexpr (!KEEP_Q) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        if constexpr (!KEEP_Q) {
+        for (int s = 0; s < NS; ++s) {
           ld8f(qsave + 32 * s, o.q[s]);
 #pragma unroll
           for (int u = 0; u < 8; ++u) o.q[s][u] = ok ? o.q[s][u] : 0.0f;
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (is_over(over, s, u)) {
-#pragma unroll 1
-            for (int x = 1; x < 16; ++x) {
-              const float dA = pick_lane(z, x & 3, L.i + 16 * (x >> 2));
-              const float qx = __shfl(o.q[s][u], (lane & 48) | x, 64), bx = __shfl(o.b[s][u], (lane & 48) | x, 64);
-              const float y = qx * fast_exp2(bx - o.b[s][u]);
-              dk[s][u] += x > L.i ? dA * y : 0.0f;
-              add_exact_score(s4, x, x > L.i ? o.k[s][u] * y : 0.0f, L);
-            }
-          }
       }
+      exact_block<true, true, true, NS, D == 128 ? 0 : 15>(over, L, o.k, o.q, o.b, z, dk, s4);
     }
     add_dv(L.w, s4);
   }
@@ -1564,6 +1622,11 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
       st_row<VEC>((bf16*)a.dp2 + at + 32 * s, pack8(dk[s]));
     }
   }
+  };
+  // at D = 128 one path for all: two of them spill more (step of 32 heads x 128 x
+  // 4096 887 -> 1085 us; at D = 64 two save 8 heads x 32K 2%)
+  if (D == 128 || chunk_steep<D>(tot)) rest(std::true_type{});
+  else rest(std::false_type{});
 }
 
 // The RoPE table of rope_cs: per channel (cos, sin) of t * base^(-2j/rope_dim),
