@@ -20,8 +20,11 @@
 // block both references are the middle of the block's range of b, so the
 // factors lie within 2^+-100 when that range is at most 200 (fact); products of
 // different blocks are accumulated in the order of the blocks and rescaled by
-// e^{difference of the references} <= 1 on the way. A difference that underflows
-// spans a whole block between the pair, whose true factor is smaller than 2^-90.
+// e^{difference of the references} <= 1 on the way. A sum may be as large as
+// 2^100 against its reference, so these factors are applied as the square of
+// their root where ranges over kSteep occur: what underflows is then below 2^-126
+// itself, not a factor that the sum's size makes up for. (Without such ranges
+// the factors alone lose pairs below 2^-94 only.)
 // A channel with a larger range takes one-sided references (factors <= 1)
 // towards the other blocks, and the block's own pairs take it term by term, with
 // the exact exponent, beside the matrix product over the other channels. Chunks
@@ -1203,13 +1206,16 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
       acc[m] = mm16(xh, zh, acc[m]);
     }
   };
+  // e^x between blocks, held as its root in the path for steep channels, and x y with it
+  auto factor = [](float x) __attribute__((always_inline)) { return fast_exp2(STEEP ? 0.5f * x : x); };
+  auto times = [](float x, float f) __attribute__((always_inline)) { return STEEP ? x * f * f : x * f; };
   auto scale_tiles = [&](floatx4 (&acc)[NM], const float* f) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       float f8[8];
       ld8f(f + 32 * s + 8 * L.g, f8);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) acc[2 * s + (u >> 2)][u & 3] *= f8[u];
+      for (int u = 0; u < 8; ++u) acc[2 * s + (u >> 2)][u & 3] = times(acc[2 * s + (u >> 2)][u & 3], f8[u]);
     }
   };
 
@@ -1219,8 +1225,8 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
   for (int s = 0; s < NS; ++s) put_row<RB>(VY, row, 4 * s + L.g, vo[s]);
   for (int x = tid; x < 3 * D; x += kNT) {
     const int u = x / D, d = x % D;
-    ek[u][d] = fast_exp2(ck[u + 1][d] - ck[u][d]);
-    eq[u][d] = fast_exp2(cq[u + 1][d] - cq[u][d]);
+    ek[u][d] = factor(ck[u + 1][d] - ck[u][d]);
+    eq[u][d] = factor(cq[u + 1][d] - cq[u][d]);
   }
   __syncthreads();
   {
@@ -1242,7 +1248,7 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
         ld8f(&ck[L.w - 1][32 * s + 8 * L.g], r8);
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          dq[s][u] = __builtin_fmaf(acc[2 * s + (u >> 2)][u & 3], fast_exp2(o.b[s][u] - r8[u]), dq[s][u]);
+          dq[s][u] += times(acc[2 * s + (u >> 2)][u & 3], factor(o.b[s][u] - r8[u]));
       }
     }
     floatx4 z = {};
@@ -1397,7 +1403,7 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
         ld8f(&cq[L.w + 1][32 * s + 8 * L.g], r8);
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          dk[s][u] = __builtin_fmaf(acc[2 * s + (u >> 2)][u & 3], fast_exp2(r8[u] - o.b[s][u]), dk[s][u]);
+          dk[s][u] += times(acc[2 * s + (u >> 2)][u & 3], factor(r8[u] - o.b[s][u]));
       }
     }
     floatx4 z = {};

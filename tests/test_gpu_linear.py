@@ -13,7 +13,7 @@ import torch
 from oracle import linear_oracle as LO
 from paper_2608_20172_amd import inputs as I
 from paper_2608_20172_amd import binding as R
-from tests.gpu_helpers import assert_close, log, to_device
+from tests.gpu_helpers import assert_close, log, rel_l2, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -426,6 +426,27 @@ def test_linear_backward_vanishing_self(H, T, D):
             rows = np.linalg.norm(x["p1r"][0, h], axis=1) + np.linalg.norm(x["p2r"][0, h], axis=1) + 32.0
             lim = 2.0 ** -8 * np.linalg.norm(ref[n], axis=1) + 2.0 ** -126 * rows
             assert np.all(err <= lim), f"{n}[0,{h}]: rows {np.flatnonzero(~(err <= lim))[:8]}, {np.max(err / lim)}"
+
+
+@pytest.mark.parametrize("span", [100.0, 190.0, 250.0])
+def test_linear_decay_between_blocks(span):
+    """A block whose channels decay by 2^-span, then a drop of 2^-40 to the next
+    block's only token, whose dg is then one term of 2^-40 to be kept: the
+    references between the blocks must not underflow before the pair's own factor
+    does. b is about -300 in log2 units, so its differences carry 2^-15 each."""
+    T, D = 17, 32
+    x = _prep(1, 2, T, D, "bf16", seed=2280)
+    g = np.full((1, 2, T, D), -span / 15 * math.log(2.0), dtype=np.float32)
+    g[:, :, 0] = 0.0
+    g[:, :, 16] = -40.0 * math.log(2.0)
+    x["g"], x["gr"] = torch.from_numpy(g).cuda(), g.astype(np.float64)
+    o = R.relation_linear_bwd(x["p1"], x["p2"], x["v"], x["g"], x["dy"])
+    torch.cuda.synchronize()
+    for h in range(2):
+        ref = LO.backward(x["p1r"][0, h], x["p2r"][0, h], x["vr"][0, h], x["gr"][0, h], x["dyr"][0, h])["dg"][16]
+        err = rel_l2(_np(o["dg"])[0, h, 16], ref)
+        log(f"  span {span} head {h}: dg of the last token relative error {err:.1e}")
+        assert err <= 2.0 ** -13
 
 
 def test_linear_self_accuracy():
