@@ -35,7 +35,9 @@
 // accuracy: an fp32 operand is split as hi + mid + lo, three bf16 numbers that
 // carry its 24 significant bits; against a bf16 input that is three exact
 // products, against another split operand the six products above 2^-24. The
-// scores, A V, Qe C0 and Kd G take operands rounded to bf16 once.
+// scores, A V, Qe C0 and Kd G take operands rounded to bf16 once, except the
+// scores of a block's own pairs in a chunk with a range over kSteep: those keep
+// fp32 accuracy, by six products or term by term.
 #include "kernels.h"
 #include "lanes.h"
 
@@ -92,6 +94,19 @@ __device__ __forceinline__ floatx4 mm32(const uintx4& a, const uintx4& b, const 
 __device__ __forceinline__ floatx4 mm16(const uintx2& a, const uintx2& b, const floatx4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(shortx4, a), __builtin_bit_cast(shortx4, b), c, 0,
                                                    0, 0);
+}
+
+// The same with fp32 operands, each as three bf16 parts: the six products above 2^-24.
+__device__ __forceinline__ floatx4 mm32_split(const float (&a)[8], const float (&b)[8], floatx4 c) {
+  uintx4 ah, am, al, bh, bm, bl;
+  split8(a, ah, am, al);
+  split8(b, bh, bm, bl);
+  c = mm32(al, bh, c);
+  c = mm32(ah, bl, c);
+  c = mm32(am, bm, c);
+  c = mm32(am, bh, c);
+  c = mm32(ah, bm, c);
+  return mm32(ah, bh, c);
 }
 
 // Byte offset of 16-byte piece ch of row `row` in a row-major bf16 array of RB
@@ -989,7 +1004,7 @@ __global__ __launch_bounds__(kNT, D <= 64 ? 3 : 2) void lin_out_kernel(LinearArg
         x[u] = STEEP && is_over(over, s, u) ? 0.0f : o.q[s][u] * fast_exp2(d);
         y[u] = STEEP && is_over(over, s, u) ? 0.0f : o.k[s][u] * fast_exp2(-d);
       }
-      at = mm32(pack8(y), pack8(x), at);
+      at = STEEP ? mm32_split(y, x, at) : mm32(pack8(y), pack8(x), at);
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) at[v] = 4 * L.g + v < L.i ? at[v] : 0.0f;
@@ -1093,6 +1108,7 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
   auto rest = [&](auto steep) __attribute__((always_inline)) {
   constexpr bool STEEP = decltype(steep)::value;
   const unsigned over = STEEP ? block_over<D>(o) : 0;
+  const bool fine = STEEP && (D < 128 || chunk_steep<D>(tot));  // the blocks' own scores keep fp32 accuracy
   {
     if (tid < D) lst[tid] = (tot[0][tid] + tot[1][tid]) + (tot[2][tid] + tot[3][tid]);  // b_last
 #pragma unroll
@@ -1414,6 +1430,27 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
 #pragma unroll
     for (int m = 0; m < NM; ++m) acc[m] = floatx4{};
     mul_block(acc, L.w, z);
+    floatx4 sf = {};  // the block's own scores with fp32 accuracy, six products
+    if (fine) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        float r8[8], x[8];
+        ld8f(&cq[L.w][32 * s + 8 * L.g], r8);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = is_over(over, s, u) ? 0.0f : o.k[s][u] * fast_exp2(r8[u] - o.b[s][u]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {  // x's parts one after the other: registers
+          const uintx4 xp = pack8(x);
+          float h[8];
+          unpack8(xp, h);
+#pragma unroll
+          for (int y = 2 - p; y >= 0; --y) sf = mm32(row_op<RB>(R + y * PS, row, 4 * s + L.g), xp, sf);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) x[u] -= h[u];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
     floatx4 s4 = {};
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -1435,6 +1472,7 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
       }
       s4 = mm32(qh, pack8(x), s4);
     }
+    if (fine) s4 = sf;
 #pragma unroll
     for (int v = 0; v < 4; ++v) s4[v] = 4 * L.g + v > L.i ? s4[v] : 0.0f;
     if (STEEP && over) {

@@ -404,7 +404,7 @@ def test_linear_backward_vanishing_self(H, T, D):
     """Rows with p2 = -f p1, whose Self S = sigmoid(-f |p1|^2 / (2 sqrt(D))) is
     small (f = 8: about 2^-33 to 2^-65), tiny (16) or 0 in fp32 (64): dp1 and dp2
     of every such row against the oracle, finite where S is 0. A row's terms are
-    products of 32-bit values; only dp1 and dp2 are rounded to bf16 (2^-9). S, the
+    products of 32-bit values; only dp1 and dp2 are rounded to bf16 (2^-8). S, the
     gradient dU of its argument and S / |p| count as 0 below 2^-126: times the rows
     that they multiply, p1 and p2 for dU and the gradients of ^p1 and ^p2 (norms
     below 32 here) for S / |p|."""
@@ -447,6 +447,36 @@ def test_linear_decay_between_blocks(span):
         err = rel_l2(_np(o["dg"])[0, h, 16], ref)
         log(f"  span {span} head {h}: dg of the last token relative error {err:.1e}")
         assert err <= 2.0 ** -13
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_linear_scores_beside_steep_channels(D):
+    """In a chunk where some channel decays by more than 2^64 over a block the
+    scores of a block's own pairs keep fp32 accuracy on every channel. p1 and p2 lie
+    on channel 0, which does not decay, channel 5 decays by 2^108, v is zero but for
+    one token of ones and dY too, so that y and dv are single scores, S_t S_j: they
+    are rounded to bf16 as a score (by up to 2^-8) and are then exact in the result.
+    Operands rounded as well would add up to 2^-7."""
+    H, T = 8 if D < 128 else 12, 17 * 64  # enough chunks for linear_bf16.hip's kernels at every width
+    rng = np.random.default_rng(2290 + D)
+    p = np.zeros((1, H, T, D))
+    p[..., 0] = rng.uniform(0.5, 3.0, (1, H, T))
+    v, dy = np.zeros((1, H, T, D)), np.zeros((1, H, T, D))
+    v[:, :, 35] = dy[:, :, 44] = 1.0
+    (p1, pr), (p2, _), (v, vr), (dy, dyr) = (to_device(z, "bf16") for z in (p, p, v, dy))
+    g = np.zeros((1, H, T, D), dtype=np.float32)
+    g[..., 5] = -108.0 / 15 * math.log(2.0)
+    gt = torch.from_numpy(g).cuda()
+    f = R.relation_linear_fwd(p1, p2, v, gt)
+    o = R.relation_linear_bwd(p1, p2, v, gt, dy)
+    torch.cuda.synchronize()
+    for h in range(H):
+        S = 1.0 / (1.0 + np.exp(-pr[0, h, :, 0] ** 2 / math.sqrt(D) / 2.0))
+        for n, got, want in (("y", _np(f["o"])[0, h, 36:48, 0], S[36:48] * S[35]),
+                             ("dv", _np(o["dv"])[0, h, 32:44, 0], S[32:44] * S[44])):
+            err = np.max(np.abs(got / want - 1.0))
+            log(f"  D={D} head {h} {n}: relative error {err:.2e}")
+            assert err <= 2.0 ** -8 * (1 + 2.0 ** -8)
 
 
 def test_linear_self_accuracy():
