@@ -18,10 +18,12 @@
 // Decay. e^{b_t - b_j} over a 16 x 16 block is factored per channel: keys carry
 // k e^{cK - b}, queries q e^{b - cQ} with a reference value per block. Inside a
 // block both references are the middle of the block's range of b, so the
-// factors lie within 2^+-100 when that range is at most 200 (fact); products of
+// factors lie within 2^+-90 when that range is at most 180 (kRange; kSteep where
+// some S of the block is below kSmallS: an operand's lowest part, 2^-16 of it,
+// then stays in the bf16 range either way); products of
 // different blocks are accumulated in the order of the blocks and rescaled by
 // e^{difference of the references} <= 1 on the way. A sum may be as large as
-// 2^100 against its reference, so these factors are applied as the square of
+// 2^90 against its reference, so these factors are applied as the square of
 // their root where ranges over kSteep occur: what underflows is then below 2^-126
 // itself, not a factor that the sum's size makes up for. (Without such ranges
 // the factors alone lose pairs below 2^-94 only.)
@@ -50,7 +52,8 @@ namespace {
 constexpr int kL = 64;       // tokens per chunk
 constexpr int kNT = 256;     // threads per workgroup
 constexpr float kSteep = 64.0f;   // log2 units of decay over a block past which a chunk takes its kernel's path for steep channels
-constexpr float kRange = 200.0f;  // log2 units over a block past which that path takes a channel term by term
+constexpr float kRange = 180.0f;  // log2 units over a block past which that path takes a channel term by term
+constexpr float kSmallS = 0x1p-10f;  // S below which a block's q and k are small: kSteep is the limit there too
 
 typedef bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -506,16 +509,16 @@ __device__ __forceinline__ bool chunk_steep(const float (*tot)[D]) {
   return wave_any(over);
 }
 
-// Bit 8 s + u (wave-uniform): the block's range of b is over kRange (or NaN) at
+// Bit 8 s + u (wave-uniform): the block's range of b is over `limit` (or NaN) at
 // element u of piece s in some lane group, four channels that then go term by term.
 template <int D>
-__device__ __forceinline__ unsigned block_over(const Own<D / 32>& o) {
+__device__ __forceinline__ unsigned block_over(const Own<D / 32>& o, float limit) {
   unsigned over = 0;
 #pragma unroll
   for (int s = 0; s < D / 32; ++s)
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (wave_any(!(bcast16<0>(o.b[s][u]) - bcast16<15>(o.b[s][u]) <= kRange))) over |= 1u << (8 * s + u);
+      if (wave_any(!(bcast16<0>(o.b[s][u]) - bcast16<15>(o.b[s][u]) <= limit))) over |= 1u << (8 * s + u);
   return __builtin_amdgcn_readfirstlane(over);
 }
 __device__ __forceinline__ bool is_over(unsigned over, int s, int u) { return (over >> (8 * s + u)) & 1; }
@@ -993,7 +996,7 @@ __global__ __launch_bounds__(kNT, D <= 64 ? 3 : 2) void lin_out_kernel(LinearArg
   // the block's own pairs
   auto own_block = [&](auto steep) __attribute__((always_inline)) {
     constexpr bool STEEP = decltype(steep)::value;
-    const unsigned over = STEEP ? block_over<D>(o) : 0;
+    const unsigned over = STEEP ? block_over<D>(o, wave_any(o.S < kSmallS) ? kSteep : kRange) : 0;
     floatx4 at = {};
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -1107,7 +1110,7 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
   scan_b<D>(o, tot, L, off);
   auto rest = [&](auto steep) __attribute__((always_inline)) {
   constexpr bool STEEP = decltype(steep)::value;
-  const unsigned over = STEEP ? block_over<D>(o) : 0;
+  const unsigned over = STEEP ? block_over<D>(o, wave_any(o.S < kSmallS) ? kSteep : kRange) : 0;
   const bool fine = STEEP && (D < 128 || chunk_steep<D>(tot));  // the blocks' own scores keep fp32 accuracy
   {
     if (tid < D) lst[tid] = (tot[0][tid] + tot[1][tid]) + (tot[2][tid] + tot[3][tid]);  // b_last
@@ -1127,8 +1130,9 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
       }
     }
   }
-  float* qsave = a.qn + ((int64_t)n * a.T + min(t, a.T - 1)) * D + 8 * L.g;  // q of a block with steep channels
-  // q is not held through the last phases at D >= 64 (registers)
+  // q is not held through the last phases at D >= 64 (registers): it comes back
+  // from its parts, or in a block with steep channels through memory
+  float* qsave = a.qn + ((int64_t)n * a.T + min(t, a.T - 1)) * D + 8 * L.g;
   constexpr bool KEEP_Q = D < 64;
   if (STEEP && !KEEP_Q && over && ok) {
 #pragma unroll

@@ -479,6 +479,27 @@ def test_linear_scores_beside_steep_channels(D):
             assert err <= 2.0 ** -8 * (1 + 2.0 ** -8)
 
 
+@pytest.mark.parametrize("H,T,D", [(1, 64, 32), (1, 17 * 64, 64), (10, 17 * 64, 128)])
+@pytest.mark.parametrize("span,bits", [(60.0, 50), (120.0, 30), (175.0, 15), (190.0, 30)])
+def test_linear_small_self_and_steep_decay(span, bits, H, T, D):
+    """Every S is 2^-bits and every channel decays by 2^-span over a block: q and k,
+    scaled by up to 2^(span / 2) either way, keep their 24 bits in dg. b reaches
+    -4 span in log2 units, so that its differences carry up to 2^-14 each."""
+    rng = np.random.default_rng(2295 + D)
+    sign = rng.choice([-1.0, 1.0], (1, H, T, D))
+    v, dy = rng.standard_normal((2, 1, H, T, D))
+    (p1, p1r), (p2, p2r) = to_device(sign, "bf16"), to_device(-2.0 * bits * math.log(2.0) / math.sqrt(D) * sign, "bf16")
+    (v, vr), (dy, dyr) = to_device(v, "bf16"), to_device(dy, "bf16")
+    g = np.full((1, H, T, D), -span / 15 * math.log(2.0), dtype=np.float32)
+    o = R.relation_linear_bwd(p1, p2, v, torch.from_numpy(g).cuda(), dy)
+    torch.cuda.synchronize()
+    for h in {0, H - 1}:
+        ref = LO.backward(p1r[0, h], p2r[0, h], vr[0, h], g[0, h].astype(np.float64), dyr[0, h])["dg"]
+        err = rel_l2(_np(o["dg"])[0, h] * 2.0 ** bits, ref * 2.0 ** bits)
+        log(f"  D={D} span {span} S 2^-{bits} head {h}: dg relative error {err:.1e}")
+        assert err <= 2.0 ** -13
+
+
 def test_linear_self_accuracy():
     """S keeps its 24 bits where it is small. Two tokens of width 32 whose p1 . p2
     are whole numbers and scale / tau_s a power of two, so that S's argument, -37
