@@ -444,7 +444,9 @@ __device__ __forceinline__ void use_raw(const LinearArgs& a, int n, int t, bool 
           gate->d[s][u] = -ea * (x > 0.0f ? sg : e * sg);
         }
       }
-      o.b[s][u] = gg * kLog2e;
+      // 2^-512 counts as 0 wherever it is a factor; sums of b stay finite and as fine as that (NaN stays)
+      const float b = gg * kLog2e;
+      o.b[s][u] = b < -512.0f ? -512.0f : b;
     }
   }
   if (!whole && !ok) {
@@ -700,7 +702,7 @@ __global__ __launch_bounds__(kNT, D == 32 || (!BWD && D == 64) ? 3 : 2) void lin
     for (int s = 0; s < NS; ++s) put_row<RB>(V, row, 4 * s + L.g, v[s]);
     const int64_t at = (int64_t)n * a.nchunks + c;
     if (tid < DA) {
-      const float lb = (tot[0][tid] + tot[1][tid]) + (tot[2][tid] + tot[3][tid]);
+      const float lb = ((tot[0][tid] + tot[1][tid]) + tot[2][tid]) + tot[3][tid];
       last[c - c0][tid] = lb;
       if (a.nseg > 1) a.gpre[at * D + a0 + tid] = fast_exp2(run);
       run += lb;
@@ -1113,7 +1115,7 @@ __global__ __launch_bounds__(kNT, 2) void lin_grad_kernel(LinearArgs a) {
   const unsigned over = STEEP ? block_over<D>(o, wave_any(o.S < kSmallS) ? kSteep : kRange) : 0;
   const bool fine = STEEP && (D < 128 || chunk_steep<D>(tot));  // the blocks' own scores keep fp32 accuracy
   {
-    if (tid < D) lst[tid] = (tot[0][tid] + tot[1][tid]) + (tot[2][tid] + tot[3][tid]);  // b_last
+    if (tid < D) lst[tid] = ((tot[0][tid] + tot[1][tid]) + tot[2][tid]) + tot[3][tid];  // b_last, as scan_b adds it
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       float k8[8], q8[8];

@@ -500,6 +500,22 @@ def test_linear_small_self_and_steep_decay(span, bits, H, T, D):
         assert err <= 2.0 ** -13
 
 
+@pytest.mark.parametrize("H,T,D", [(2, 150, 32), (1, 17 * 64 + 5, 64), (10, 17 * 64 - 3, 128)])
+@pytest.mark.parametrize("low", [-1e4, -1e30, float(np.finfo(np.float32).min), -math.inf])
+def test_linear_reset_by_lowest_retention(low, H, T, D):
+    """A log-retention that clears the state (alpha = 0), down to the type's lowest
+    value, on all channels of some tokens and on single channels of others, several
+    in a chunk: y, the state and every gradient against the oracle."""
+    x = _prep(1, H, T, D, "bf16", seed=2300 + T + D, gmax=0.05)
+    g = x["gr"].astype(np.float32)
+    g[:, :, 20::50] = low
+    g[:, :, 33::40, 3::7] = low
+    x["g"] = torch.from_numpy(g).cuda()
+    x["gr"] = np.maximum(g.astype(np.float64), -1e5)  # exp is 0 either way
+    check_linear_fwd(x, "bf16", heads=[(0, 0)])
+    check_linear_bwd(x, "bf16", heads=[(0, 0)])
+
+
 def test_linear_self_accuracy():
     """S keeps its 24 bits where it is small. Two tokens of width 32 whose p1 . p2
     are whole numbers and scale / tau_s a power of two, so that S's argument, -37
