@@ -219,7 +219,7 @@ hipError_t launch_linear_fwd(const LinearArgs& a, int dtype, hipStream_t stream)
 hipError_t launch_linear_bwd(const LinearArgs& a, int dtype, hipStream_t stream);
 // bf16 inputs (linear_bf16.hip): chunks per segment of its state kernel, and the passes.
 int linear_bf16_segment(int64_t heads, int nchunks);
-bool linear_bf16_route(int64_t heads, int nchunks, int D, bool gated, bool rope, bool backward);
+bool linear_bf16_route(int64_t heads, int nchunks, int D, bool gated, int rope_dim, bool backward);
 int linear_bf16_rope_row(int rope_dim);  // (cos, sin) entries per row of the bf16 kernels' RoPE table
 hipError_t launch_linear_bf16_rope_table(float2* tab, int nchunks, int rope_dim, double base, hipStream_t stream);
 hipError_t launch_linear_bf16_fwd(const LinearArgs& a, hipStream_t stream);

@@ -1734,18 +1734,36 @@ int linear_bf16_segment(int64_t heads, int nchunks) {
 // Which bf16 problems this file's kernels take; linear.hip's take the rest.
 // Theirs share a chunk among more waves and scan up to 16 chunks a head in one
 // launch; with few chunks in all that shorter chain is the whole time. The gate
-// costs their width-128 backward a row pass, and RoPE costs them barriers.
-// Measured (us, linear.hip against this file; backward: with the forward):
-// width 128 backward 53 and 81 at 4 chunks, 63 and 95 at 32, 105 and 115 at 128,
-// 172 and 133 at 256; gated 75 and 90 at 4, 91 and 97 at 32, 109 and 104 at 32 (16
-// a head), 152 and 125 at 128. Width 128 forward 21 and 24 at 4, 31.6 and 34.7 at
-// 256, 28.2 and 28.0 with 32 a head; with RoPE 31 and 30 at 4, 41.5 and 43.1 at
-// 256. Width 64 backward 48 and 52 at 128, 51.6 and 55.9 at 256, 81 and 72 at 512,
-// 60 and 56 with 32 a head; with RoPE 65 and 65 at 128. Width 32: no slower here.
-bool linear_bf16_route(int64_t heads, int nchunks, int D, bool gated, bool rope, bool backward) {
+// costs their width-128 backward a row pass, RoPE costs them barriers, and here
+// RoPE over part of the width costs an exchange through LDS. Width 32 is
+// faster here throughout. Measured with the gate (us per replayed graph of the
+// call, linear.hip / this file; n/c: n chunks in all, c a head):
+//   width 64 forward   10/5 20.4 / 20.9, 512/16 31.4 / 31.6, 1024/16 48.1 / 47.9, 36/18 23.3 / 21.6, 2/1 19.6 / 17.1
+//     RoPE over 60     10/5 27.5 / 29.0, 1024/16 60.2 / 62.3, 36/18 30.6 / 29.9, 2/1 27.2 / 25.0; over 64 10/5 27.6 / 26.8
+//   width 64 backward  36/18 40.3 / 38.7, 320/5 65.1 / 56.2; 128 and 256 chunks of up to 16 a head, with the forward and
+//     not replayed, 48 / 52 and 51.6 / 55.9
+//     RoPE over 60     10/5 45.2 / 48.9, 256/16 55.0 / 57.0, 36/18 50.8 / 49.8, 320/5 78.9 / 67.9, 2/1 44.7 / 41.1
+//     over 64          64/8 46.1 / 45.3; channels that forget fast among them 20/5 48.7 / 51.1, 80/5 50.6 / 52.3,
+//                      128/8 52.9 / 53.9, 128/2 55.4 / 53.0
+//   width 128 forward  144/18 40.8 / 42.8, 64/32 34.0 / 36.2, 256/32 43.3 / 43.5, 288/18 64.4 / 56.1
+//     RoPE over 80     10/5 35.5 / 38.9, 256/16 47.2 / 53.1, 144/18 49.7 / 53.0, 512/16 79.1 / 80.7, 64/1 47.1 / 32.1
+//     over 128         256/16 49.4 / 51.1, 144/18 52.3 / 51.7
+//   width 128 backward 64/2 80.7 / 87.3, 72/18 116.8 / 97.1, 256/16 without the gate 129 / 105
+//     RoPE over 80     64/2 88.1 / 99.2, 64/16 96.9 / 106, 72/18 123 / 109, 64/1 86.6 / 69.9
+bool linear_bf16_route(int64_t heads, int nchunks, int D, bool gated, int rope_dim, bool backward) {
   const int64_t chunks = heads * nchunks;
-  if (D == 128 && backward) return chunks > (gated ? 32 : 160);
-  if (D < (backward ? 64 : 128) || rope) return true;
+  const bool full = rope_dim == D, part = rope_dim > 0 && !full;
+  const bool scan16 = nchunks > 1 && nchunks <= 16;  // linear.hip scans in one launch, and there is something to scan
+  if (D == 32) return true;
+  if (D == 128 && backward) return chunks > (!gated ? 160 : nchunks == 1 ? 32 : 64);
+  if (D == 128) {
+    if (chunks > 256) return true;
+    if (nchunks <= 16) return nchunks == 1 && rope_dim > 0;
+    return full || chunks > 160 || nchunks > 32;
+  }
+  if (!backward) return full || !scan16 || chunks > (part ? 1024 : 512);
+  if (full) return nchunks <= 2 || nchunks > 8 || chunks > 80;
+  if (part) return !scan16 || chunks > 256;
   return nchunks > 16 || chunks > 256;
 }
 

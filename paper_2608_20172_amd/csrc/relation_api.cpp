@@ -1338,9 +1338,9 @@ static rel_status check_rope(const rel_problem* p, int32_t rope_dim, float rope_
 }
 
 // Whether linear_bf16.hip's kernels take the problem.
-static bool linear_bf16(const rel_problem* p, bool gated, bool rope, bool backward) {
+static bool linear_bf16(const rel_problem* p, bool gated, int32_t rope_dim, bool backward) {
   return p->dtype == REL_BF16 &&
-         rel::linear_bf16_route(p->B * p->H, linear_chunks(p), (int)p->D, gated, rope, backward);
+         rel::linear_bf16_route(p->B * p->H, linear_chunks(p), (int)p->D, gated, (int)rope_dim, backward);
 }
 
 // What a call uses with the kernels of linear_bf16.hip (bf16) or linear.hip. The
@@ -1441,7 +1441,7 @@ static rel_status linear_fwd_impl(const rel_problem* p, const void* p1, const vo
   a.nseg = linear_segments(p);
   a.vec16 = linear_vec16(p, {p1, p2, v, a_log, dt_bias}, g);
   const bool gated = a_log != nullptr;
-  const LinearPlan L = linear_plan(p, linear_bf16(p, gated, rope_dim > 0, false), false, gated, rope_dim);
+  const LinearPlan L = linear_plan(p, linear_bf16(p, gated, rope_dim, false), false, gated, rope_dim);
   set_linear_workspace(a, L, (char*)workspace, false);
   REL_TRY(set_rope(a, p, rope_dim, rope_base, (char*)workspace, L.rope, (hipStream_t)stream));
   const hipError_t e = rel::launch_linear_fwd(a, p->dtype, (hipStream_t)stream);
@@ -1516,7 +1516,7 @@ static rel_status linear_bwd_impl(const rel_problem* p, const void* p1, const vo
                             {ddt_bias, pb, false, true, "ddt_bias"},
                             {workspace, need, false, true, "workspace"}}));
   if (test_fail_launch()) return fail(REL_ERR_HIP, "launch failure injected by RELATION_TEST_FAIL_LAUNCH");
-  const LinearPlan L = linear_plan(p, linear_bf16(p, gated, rope_dim > 0, true), true, gated, rope_dim);
+  const LinearPlan L = linear_plan(p, linear_bf16(p, gated, rope_dim, true), true, gated, rope_dim);
   rel::LinearArgs a{};
   a.p1 = p1; a.p2 = p2; a.v = v; a.g = g; a.dy = dout;
   a.dp1 = dp1; a.dp2 = dp2; a.dv = dv; a.dg = dg;

@@ -81,3 +81,30 @@ def test_workspace_for_a_sequence_serves_shorter_ones(lib, D, H):
             size = getattr(lib, f"relation_linear_gated_{'bwd' if backward else 'fwd'}_workspace_bytes")(p, 24)
             assert size >= last, (T, size, last)
             last = size
+
+
+# (B H, T, D, gated, rope, backward) -> linear_bf16.hip's kernels; both sides of each line of linear_bf16_route
+ROUTES = [
+    ((1, 64, 32, True, 24, True), True), ((2, 300, 32, False, 0, False), True),
+    ((2, 64, 64, False, 0, False), True), ((2, 65, 64, False, 0, False), False), ((32, 1024, 64, True, 0, False), False),
+    ((33, 1024, 64, True, 0, False), True), ((2, 1025, 64, False, 0, False), True),
+    ((64, 1024, 64, True, 60, False), False), ((65, 1024, 64, True, 60, False), True), ((2, 300, 64, True, 64, False), True),
+    ((16, 1024, 64, False, 0, True), False), ((17, 1024, 64, False, 0, True), True), ((1, 1025, 64, False, 0, True), True),
+    ((16, 1024, 64, True, 60, True), False), ((17, 1024, 64, True, 60, True), True), ((2, 64, 64, True, 60, True), True),
+    ((10, 512, 64, True, 64, True), False), ((11, 512, 64, True, 64, True), True), ((2, 128, 64, True, 64, True), True),
+    ((1, 576, 64, True, 64, True), True),
+    ((16, 1024, 128, False, 0, False), False), ((17, 1024, 128, False, 0, False), True), ((8, 1088, 128, False, 0, False), False),
+    ((10, 1088, 128, False, 0, False), True), ((1, 2112, 128, False, 0, False), True), ((2, 64, 128, True, 80, False), True),
+    ((8, 1088, 128, True, 80, False), False), ((1, 1088, 128, True, 128, False), True), ((4, 300, 128, True, 128, False), False),
+    ((10, 1024, 128, False, 0, True), False), ((10, 1088, 128, False, 0, True), True), ((4, 1024, 128, True, 80, True), False),
+    ((4, 1088, 128, True, 80, True), True), ((32, 64, 128, True, 0, True), False), ((33, 64, 128, True, 0, True), True),
+]
+
+
+@pytest.mark.parametrize("problem,bf16_kernels", ROUTES)
+def test_which_kernels_take_a_bf16_problem(lib, problem, bf16_kernels):
+    H, T, D, gated, rope, backward = problem
+    _used(lib, 1, H, T, D, R.REL_BF16, backward, gated, rope)
+    assert bool(lib.probe_bf16_kernels()) == bf16_kernels
+    _used(lib, 1, H, T, D, R.REL_F32, backward, gated, rope)
+    assert not lib.probe_bf16_kernels()
