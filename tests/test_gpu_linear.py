@@ -14,6 +14,7 @@ from oracle import linear_oracle as LO
 from paper_2608_20172_amd import inputs as I
 from paper_2608_20172_amd import binding as R
 from tests.gpu_helpers import assert_close, log, rel_l2, to_device
+from tests.linear_shapes import BF16_KERNELS
 
 pytestmark = pytest.mark.gpu
 
@@ -539,6 +540,44 @@ def test_linear_self_accuracy():
         err = np.max(np.abs(_np(o["dg"])[0, h, 1] / ref["dg"][1] - 1.0))
         log(f"  S argument {-(600 + 40 * h) / 16}: dg relative error {err:.1e}")
         assert err <= 24 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("H,T,D,rope,aligned", BF16_KERNELS)
+def test_linear_bf16_gated(H, T, D, rope, aligned):
+    """linear_bf16.hip's kernels with the gate and RoPE over none, part (halves that
+    are and are not multiples of 4 and 8) or all of the width, rows and parameters
+    on and off 16-byte boundaries, gradients bit for bit the same when repeated: the
+    first and the last head against the oracle."""
+    from oracle import layer_oracle as LR
+    x = _prep(1, H, T, D, "bf16", seed=2400 + T + D + rope)
+    rng = np.random.default_rng(2401 + rope)
+    r = (2.0 * rng.standard_normal((1, H, T, D))).astype(np.float32)
+    a_log, dt_bias = _gate_params(H, D, 2402 + rope)
+    rt, at, bt = (torch.from_numpy(z).cuda() for z in (r, a_log, dt_bias))
+    args = [x["p1"], x["p2"], x["v"], rt, at, bt, x["dy"]]
+    if not aligned:
+        args = [_misaligned(z) for z in args]
+    log(f"[linear bf16 gated] H={H} T={T} D={D} rope={rope} aligned={aligned}")
+    f = R.relation_linear_gated_fwd(*args[:6], rope_dim=rope, want_state=True)
+    o = R.relation_linear_gated_bwd(*args, rope_dim=rope)
+    again = R.relation_linear_gated_bwd(*args, rope_dim=rope)
+    torch.cuda.synchronize()
+    for n in o:
+        assert torch.equal(o[n], again[n]), n
+    turn = lambda z: np.concatenate([LR.rope(z[:, :rope], 1e4), z[:, rope:]], 1) if rope else z
+    back = lambda z: np.concatenate([LR.rope_transpose(z[:, :rope], 1e4), z[:, rope:]], 1) if rope else z
+    for h in {0, H - 1}:
+        p1r, p2r = turn(x["p1r"][0, h]), turn(x["p2r"][0, h])
+        g = LO.kda_gate(r[0, h], a_log[h], dt_bias[h])
+        rf = LO.forward(p1r, p2r, x["vr"][0, h], g)
+        rb = LO.backward(p1r, p2r, x["vr"][0, h], g, x["dyr"][0, h])
+        gb = LO.kda_gate_backward(r[0, h], a_log[h], dt_bias[h], rb["dg"])
+        assert_close(f"y[{h}]", _np(f["o"])[0, h], rf["Y"], "bf16")
+        assert_close(f"state[{h}]", _np(f["state"])[0, h], rf["C"], "bf16")
+        for n, ref in (("dp1", back(rb["dp1"])), ("dp2", back(rb["dp2"])), ("dv", rb["dv"]), ("dr", gb["dr"])):
+            assert_close(f"{n}[{h}]", _np(o[n])[0, h], ref, "bf16")
+        for n, terms in (("da_log", rb["dg"] * g), ("ddt_bias", gb["dr"])):
+            _assert_param_grad(n, _np(o[n])[None, h], gb[n][None], terms[None, None], "bf16")
 
 
 @pytest.mark.parametrize("rope", [24, 26, 28, 30, 32])

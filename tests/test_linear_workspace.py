@@ -11,6 +11,7 @@ import pytest
 
 from paper_2608_20172_amd import binding as R
 from paper_2608_20172_amd import build
+from tests.linear_shapes import BF16_KERNELS
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 BASE, GB = 0x7F0000000000, 1 << 33
@@ -108,3 +109,10 @@ def test_which_kernels_take_a_bf16_problem(lib, problem, bf16_kernels):
     assert bool(lib.probe_bf16_kernels()) == bf16_kernels
     _used(lib, 1, H, T, D, R.REL_F32, backward, gated, rope)
     assert not lib.probe_bf16_kernels()
+
+
+def test_shapes_of_the_gpu_tests_take_the_bf16_kernels(lib):
+    for H, T, D, rope, _ in BF16_KERNELS:
+        for backward in (False, True):
+            _used(lib, 1, H, T, D, R.REL_BF16, backward, True, rope)
+            assert lib.probe_bf16_kernels(), (H, T, D, rope, backward)
