@@ -372,18 +372,21 @@ __device__ __forceinline__ bool wave_any(bool p) { return __any((int)p); }
 // 8192, D = 96 forward 256 -> 220 us, backward 885 -> 726; N = 4, T = 8192, D =
 // 64 144 -> 134 and 408 -> 396; N = 36, T = 2048 50 -> 46 (forward). With one
 // place of 15 empty or fewer the shared L2 is worth more: N = 60, T = 2048, D =
-// 128 forward 92 against 94 us, N = 100, T = 1024 35 against 44.
+// 128 forward 92 against 94 us, N = 100, T = 1024 35 against 44. So it is with 8
+// or more heads on an XCD: N = 57, D = 128, T = 2048 forward 89 against 100 us, N =
+// 65, D = 96, T = 512 21 against 23, N = 58, D = 64, T = 512 backward 42 against 44
+// (at T = 2048 some backwards gain up to 5%: N = 66, D = 96).
 // ---------------------------------------------------------------------------
 struct TileMap {
   int N, ntiles, hpx;  // heads, tiles per head, heads per XCD (0: heads alternate)
 };
-constexpr int kSpreadWaste = 12;  // heads alternate when more than N / 12 of the XCDs' places for heads stay empty
+constexpr int kSpreadWaste = 12;  // up to 56 heads alternate when more than N / 12 of the XCDs' places for heads stay empty
 __host__ __device__ inline TileMap make_tilemap(int N, int ntiles) {
   TileMap m;
   m.N = N;
   m.ntiles = ntiles;
   m.hpx = (N + 7) / 8;
-  if ((8 * m.hpx - N) * kSpreadWaste > N) m.hpx = 0;
+  if (m.hpx < 8 && (8 * m.hpx - N) * kSpreadWaste > N) m.hpx = 0;
   return m;
 }
 __host__ __device__ inline long grid_size(const TileMap& m) { return (m.hpx ? 8L * m.hpx : (long)m.N) * m.ntiles; }
