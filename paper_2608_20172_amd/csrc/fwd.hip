@@ -574,10 +574,12 @@ __global__ __launch_bounds__(kNT, (fwd_split_occupancy<P, D>())) void fwd_split_
 // and 8.6 at 128, 10.4 and 10.6 at 192 (T = 256); D = 96 11.5 and 13.1 at 128.
 // Below 256 tokens a 128-row workgroup has one or two tiles: fp32 layers of 55 x 2
 // heads x 125 at D = 64 lost 2% with the split, D = 64 in bf16 7.8 and 7.4 at 128.
+// Up to 64 tokens there is one tile and nothing to share (fp32, 2 heads x 64 x 64,
+// per replayed graph: 17.6 and 18.3).
 template <class P, int D>
 int64_t few_tiles(int T) {
   const int64_t most = sizeof(typename P::T) == 2 && D > 64 ? 128 : 256;
-  return T >= 1024 ? most : T >= 256 ? most / 2 : most / 4;
+  return T >= 1024 ? most : T >= 256 ? most / 2 : T > kBK ? most / 4 : 0;
 }
 
 template <class P, int D>
