@@ -1795,7 +1795,9 @@ hipError_t launch_gate_bwd(const LinearArgs& a, bool row_pass, hipStream_t strea
 template <typename TI>
 hipError_t launch_bwd_t(const LinearArgs& a, hipStream_t stream) {
   switch (a.D) {
-    case 32: return launch_bwd_d<TI, 32>(a, stream);
+    case 32:  // in bf16 never here (linear_bf16_route)
+      if constexpr (!kBF<TI>) return launch_bwd_d<TI, 32>(a, stream);
+      return hipErrorInvalidValue;
     case 64: return launch_bwd_d<TI, 64>(a, stream);
     case kSW: return launch_bwd_split<TI>(a, stream);
     default: return hipErrorInvalidValue;
@@ -1817,7 +1819,9 @@ hipError_t launch_fwd_d(const LinearArgs& a, hipStream_t stream) {
 template <typename TI>
 hipError_t launch_fwd_t(const LinearArgs& a, hipStream_t stream) {
   switch (a.D) {
-    case 32: return launch_fwd_d<TI, 32>(a, stream);
+    case 32:  // in bf16 never here (linear_bf16_route)
+      if constexpr (!kBF<TI>) return launch_fwd_d<TI, 32>(a, stream);
+      return hipErrorInvalidValue;
     case 64: return launch_fwd_d<TI, 64>(a, stream);
     case 128: return launch_fwd_d<TI, 128>(a, stream);
     default: return hipErrorInvalidValue;
