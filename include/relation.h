@@ -345,13 +345,17 @@ rel_status relation_decode_merge(const rel_problem* p, int32_t nstates, const fl
  *   workspace  relation_linear_fwd_workspace_bytes(p) bytes, 16-byte aligned:
  *              fp32, per chunk of 64 tokens its state contribution and retention
  *              product, and the state entering it; per segment of 16 chunks
- *              the scan's summary. bf16: per chunk the state entering it from a
- *              zero start of its segment (1 to 8 chunks) and its retention, per
- *              segment the result (all in 32 bits).
+ *              the scan's summary. bf16: the larger of this and what the bf16
+ *              kernels keep (per chunk the state entering it from a zero start
+ *              of its segment of 1 to 8 chunks and its retention, per segment
+ *              the result, all in 32 bits), whichever kernels take the
+ *              problem, so that the size for a sequence serves shorter ones.
  * Precision: fp32 inputs run every product in fp32. bf16 inputs take the
  * chunk products on bf16 operands with fp32 accumulation, except that the
  * backward keeps fp32 accuracy in the products that reach dg (and so dr,
- * dA_log, d dt_bias); decay weights, state scans and statistics are fp32. */
+ * dA_log, d dt_bias), and that the pairs of a 16-token block in a chunk where a
+ * channel decays by more than 2^64 over one do so in both directions; decay
+ * weights, state scans and statistics are fp32. */
 size_t relation_linear_fwd_workspace_bytes(const rel_problem* p);
 rel_status relation_linear_fwd(const rel_problem* p, const void* p1, const void* p2, const void* v,
                                const float* g, void* out, float* state_out, void* workspace,
@@ -360,8 +364,9 @@ rel_status relation_linear_fwd(const rel_problem* p, const void* p1, const void*
 /* Linear Relation backward: gradients of sum(dout * y) with respect to p1,
  * p2, v (dtype, the problem's strides) and g (fp32, dense [B,H,T,D]). The
  * chunk states are recomputed from the inputs. D in {32, 64, 128}. At D = 128
- * with fp32 inputs the state is taken as four 64 x 64 blocks (halves of the relation and of
- * the information channels), each of which evolves on its own, and the
+ * fp32 problems, and bf16 ones of few chunks, take the state as four 64 x 64
+ * blocks (halves of the relation and of the information channels), each of
+ * which evolves on its own, and the
  * gradient is the sum of the four blocks' terms; the result matches the
  * one-block computation up to fp32 rounding order. Head widths between these
  * (the paper's 48, 60, 80) run zero-padded to the next one, with an explicit
@@ -369,12 +374,12 @@ rel_status relation_linear_fwd(const rel_problem* p, const void* p1, const void*
  *   workspace  relation_linear_bwd_workspace_bytes(p) bytes, 16-byte aligned:
  *              the forward workspace plus, per chunk, the D x D products that
  *              the reverse scan over chunks reads and the state gradients it
- *              writes, and per segment the reverse summary. bf16 at D >= 64
- *              adds one fp32 plane for channels of steep decay. fp32 at
- *              D = 128: the chunk states are those of 4 B H heads of width 64,
- *              plus S ^p1 and S ^p2 of every row and eight fp32 [B,H,T,128]
- *              planes of partial gradients (5 KiB per token and head). At
- *              D = 128 the size is at least ten fp32 planes in both types. */
+ *              writes, and per segment the reverse summary. At D = 128 the
+ *              chunk states are those of 4 B H heads of width 64, and S ^p1
+ *              and S ^p2 of every row and eight fp32 [B,H,T,128] planes of
+ *              partial gradients (5 KiB per token and head) come with them.
+ *              bf16: the larger of this and what the bf16 kernels need, as for
+ *              the forward. */
 size_t relation_linear_bwd_workspace_bytes(const rel_problem* p);
 rel_status relation_linear_bwd(const rel_problem* p, const void* p1, const void* p2, const void* v,
                                const float* g, const void* dout, void* dp1, void* dp2, void* dv, float* dg,
@@ -398,7 +403,8 @@ rel_status relation_linear_bwd(const rel_problem* p, const void* p1, const void*
  * Forward: as relation_linear_fwd, with workspace
  * relation_linear_gated_fwd_workspace_bytes(p, rope_dim) (the ungated
  * forward's plus a table of (cos, sin) at the 64-token chunk starts and at
- * the offsets inside a chunk, ((T + 63)/64 + 64) x rope_dim/2). Backward: as
+ * the offsets inside a chunk, ((T + 63)/64 + 64) x rope_dim/2; for the bf16
+ * kernels one entry per channel, rope_dim rounded up to 8). Backward: as
  * relation_linear_bwd, the gradients with respect to the unrotated p1, p2, with
  *   dr         [B,H,T,D] fp32, dense: dL/dr (in place of dg);
  *   da_log,    [H,D] fp32: dL/dA_log and dL/d dt_bias, each summed over batch

@@ -570,7 +570,9 @@ __global__ __launch_bounds__(kNT, (fwd_split_occupancy<P, D>())) void fwd_split_
 // times at the limit and past it (us, 128 against 32 rows), T >= 1024, where the
 // chain is long: D = 64 23.1 and 20.5 at 256, 24.2 and 29.4 at 384 (T = 1024);
 // where one 32-row workgroup fills a CU's LDS in bf16 D = 96 25.2 and 22.1 at
-// 128, 25.7 and 29.1 at 160; fp32 D = 64 159 and 123 at 256. Shorter: D = 64 10.2
+// 128, 25.7 and 29.1 at 160; fp32 D = 64 159 and 123 at 256. Longer rows at the
+// limit gain more (per replayed graph): D = 64 4 x 8192 135 and 91, 1 x 32768 509 and
+// 322; D = 128 2 x 8192 169 and 119; fp32 D = 64 4 x 8192 1227 and 758. Shorter: D = 64 10.2
 // and 8.6 at 128, 10.4 and 10.6 at 192 (T = 256); D = 96 11.5 and 13.1 at 128.
 // Below 256 tokens a 128-row workgroup has one or two tiles: fp32 layers of 55 x 2
 // heads x 125 at D = 64 lost 2% with the split, D = 64 in bf16 7.8 and 7.4 at 128.

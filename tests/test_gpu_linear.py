@@ -611,8 +611,9 @@ def test_linear_bf16_blocks_and_segments(H, T, D, steep):
     and a run of eight) decay by up to e^-20 per token, past the range that the
     products' reference points cover, and the others stay slow.
 
-    A rounding to bf16 changes a value by at most 2^-9 of it, and so, over sums
-    whose terms it changes independently, the result's relative l2 by as much.
+    A rounding to bf16 changes a value by at most 2^-8 of it, by less than 2^-9 in
+    the root mean square, and so, over sums whose terms it changes independently, the
+    result's relative l2.
     state: the write k e^(b_end - b) is rounded once; y: that, the scores' two
     operands and y itself; dv: its scores' two operands, the scores and dv
     itself; dp1 and dp2: only they themselves, as their products keep fp32
